@@ -211,6 +211,23 @@ int mrt_get_tile(const mrt_ctx* ctx, int* rows_per_item, int* grid_blocks);
 int mrt_set_steps_per_pass(mrt_ctx* ctx, int steps, int rows);
 int mrt_get_steps_per_pass(const mrt_ctx* ctx, int* steps, int* rows);
 
+/* The level pipeline: four time steps per kernel launch on any grid and in
+ * every precision (default scheme only).  A block advances a band of rows
+ * with one group of waves per time level, the levels handing rows to each
+ * other through LDS, so that the state crosses the memory interface once per
+ * four steps.  With it on, mrt_step(n) runs n / 4 such passes and the
+ * remaining steps by the form of mrt_set_steps_per_pass.  Results equal single
+ * steps to rounding order (bit-identical in the FP32 storage forms, as
+ * measured).  rows: band height (0: by grid size), -1 turns it off.
+ * mrt_init_grid turns it on where it is expected to be faster (from about
+ * 400 x 300 cells on in FP64, 600^2 in FP32 storage; not on the tube march's
+ * grids); mrt_autotune times it too, and mrt_set_steps_per_pass, which names
+ * another form, turns it off.
+ * mrt_get_pipeline gives the band height, -1 when off.  Errors: MRT_EINVAL
+ * (rows < -1). */
+int mrt_set_pipeline(mrt_ctx* ctx, int rows);
+int mrt_get_pipeline(const mrt_ctx* ctx, int* rows);
+
 /* Scheme variants (the paper's discretisation passage admits three
  * readings; section "Construction", last paragraph before Fig. 1):
  *   0                      unsplit forward Euler, per-axis Lax-Wendroff

@@ -18,6 +18,7 @@
 
 #include "mrt_dual.h"
 #include "mrt_internal.h"
+#include "mrt_pipe.h"
 #include "mrt_tube.h"
 #include "../../include/mrtlb.h"
 
@@ -30,6 +31,8 @@ hipError_t k_step2(int prec, const Inst* insts, const Item* items, int nitems, c
                    void* fout, unsigned* health, int grid, bool nt, bool wrap4, hipStream_t st);
 hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, const void* fin,
                   void* fout, unsigned* health, int grid, bool nt, int ny, hipStream_t st);
+hipError_t k_pipe(int prec, int waves, const Inst* insts, const Item* items, int nitems, const void* fin,
+                  void* fout, unsigned* health, bool nt, hipStream_t st);
 hipError_t k_variant(int prec, const Inst* P, int nx, int ny, int scheme, bool reflect,
                      const void* fin, void* fout, void* tmp, unsigned* health, hipStream_t st);
 hipError_t k_adjoint(int prec, const Inst* insts, const Item* items, int nitems, const void* lin,
@@ -54,6 +57,7 @@ hipError_t k_import(int prec, const Inst* P, long long cells, const double* in, 
 
 using mrt::Inst;
 using mrt::Item;
+using mrt::kPipeSteps;
 using mrt::kTubeSteps;
 using mrt::kTubeWidth;
 
@@ -292,13 +296,13 @@ hipError_t run_graphs(GraphCache& cache, int& cur, int n, hipStream_t stream, En
     return hipSuccess;
 }
 
-// Work items of one instance: 256-column chunks x ceil(ny / rows) bands of
+// Work items of one instance: `width`-column chunks x ceil(ny / rows) bands of
 // nearly equal height (at most `rows` rows, heights differ by at most 1).
-void add_items(std::vector<Item>& items, int inst, int nx, int ny, int rows) {
+void add_items(std::vector<Item>& items, int inst, int nx, int ny, int rows, int width = 256) {
     const long long nb = (ny + rows - 1) / rows;
     for (long long k = 0; k < nb; ++k) {
         const int y0 = int(k * ny / nb), y1 = int((k + 1) * ny / nb);
-        for (int x0 = 0; x0 < nx; x0 += 256) items.push_back(Item{inst, x0, y0, y1});
+        for (int x0 = 0; x0 < nx; x0 += width) items.push_back(Item{inst, x0, y0, y1});
     }
 }
 
@@ -351,6 +355,60 @@ bool two_step_default(int nx, int ny, bool beyond_cache) {
     return beyond_cache || two_step_items(nx, ny, 8) >= kTwoStepSlots[0];
 }
 
+// Launch shape of the level pipeline: waves per level (a block is 4 x waves
+// waves and stores pipe_width(waves) columns), band height, and the row
+// iterations of a launch.  Resident blocks fill the chip `slots` at a time
+// (sixteen waves per CU in FP32 storage, eight in FP64); a block marches its
+// band's rows plus the pipeline's fill and overlap, 3 kPipeSteps - 1 rows, and
+// an iteration of a full CU takes the same time for either width.  The shape
+// with the fewest rounds x (rows + fill) wins: two waves on grids of a few
+// thousand columns and less (1024^2: 30 iterations against 32, 19.3 against
+// 20.2 us per step), four on wider ones (4096^2: 285 against 304, 197 against
+// 210 us), which recompute 3 % of the columns instead of 7 %.
+struct PipeShape {
+    int waves = 2, rows = 1;
+    long long cost = -1;
+};
+constexpr long long kPipeFill = 3 * kPipeSteps - 1;
+
+PipeShape pipe_shape(int nx, int ny, int prec, int rows) {
+    PipeShape best;
+    for (int waves : {2, 4}) {
+        if (waves == 4 && prec == MRT_FP64) break;
+        const long long slots = 256 * (prec == MRT_FP64 ? 2 : 4) / waves;
+        const long long chunks = (nx + mrt::pipe_width(waves) - 1) / mrt::pipe_width(waves);
+        for (long long rounds = 1; rounds <= 64; ++rounds) {
+            long long bands = std::min<long long>(ny, slots * rounds / chunks);
+            if (rows > 0) bands = (ny + rows - 1) / rows;
+            if (bands < 1) continue;
+            const long long r = (ny + bands - 1) / bands;
+            const long long n = rows > 0 ? (chunks * bands + slots - 1) / slots : rounds;
+            const long long cost = n * (r + kPipeFill);
+            if (best.cost < 0 || cost < best.cost) best = PipeShape{waves, int(r), cost};
+            if (rows > 0) break;
+        }
+    }
+    return best;
+}
+
+// Whether a grid runs the level pipeline by default: where its launch, cost
+// row iterations for four steps, is expected to be shorter than four steps of
+// the form it would run otherwise (per_pass 1 or 2).  Microseconds of one
+// iteration and site updates per microsecond of the other forms as measured
+// (FP64, FP32, FP32 with FP64 collision); the one-step kernel adds its launch.
+// Measured per step, other form -> pipeline: FP64 360 x 100 5.6 -> 5.9
+// (stays), 400 x 300 11.4 -> 7.8, 512^2 15.4 -> 10.8, 1024^2 39.3 -> 22.9,
+// 4096^2 575 -> 282; FP32 with FP64 collision 512^2 9.4 -> 10.2 (stays), 700^2
+// 16.2 -> 12.4, 1024^2 22.2 -> 19.3, 4096^2 279 -> 198; FP32 512^2 9.9 -> 10.1
+// (stays), 700^2 17.2 -> 12.1, 4096^2 312 -> 205.
+bool pipe_default(int nx, int ny, int prec, int per_pass, const PipeShape& shape) {
+    const double iteration[3] = {2.0, 2.4, 2.45};
+    const double rate1[3] = {18500, 33000, 35000}, rate2[3] = {28000, 53000, 54000};
+    const double cells = (double)nx * ny;
+    const double other = per_pass == 2 ? cells / rate2[prec] : 2.2 + cells / rate1[prec];
+    return shape.cost * iteration[prec] / kPipeSteps < other;
+}
+
 // Band height of the batch's two-step kernel when none is given.
 constexpr int kBatchRows2 = 32;
 
@@ -395,6 +453,11 @@ struct mrt_ctx {
     Item* d_items4 = nullptr;        // work items of the tube march
     int nitems4 = 0;
     GraphCache graphs4;              // captured tube-march passes
+    bool pipe = false;               // four steps at a time by the level pipeline
+    Item* d_items_p = nullptr;       // its work items
+    int nitems_p = 0, rows_p = 0, waves_p = 2;
+    GraphCache graphs_p;             // captured pipeline passes
+    bool ghosts_stale = false;       // reflecting-wall ghosts of the current state (the pipeline writes none)
     bool eager = false;              // launch step by step (the tile autotuner)
     int scheme = 0;                  // MRT_SCHEME_* flags
     void* f_tmp = nullptr;           // post-collision state of the split scheme
@@ -435,6 +498,7 @@ int fill_ghosts(mrt_ctx* c) {
     }
     if (has_kind(c->bc, MRT_BC_REFLECT))
         HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, perim, c->f[c->cur], 1, c->stream));
+    c->ghosts_stale = false;
     return MRT_OK;
 }
 
@@ -497,6 +561,21 @@ int build_items4(mrt_ctx* c) {
     HIPTRY(hipMemcpy(c->d_items4, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
     c->nitems4 = int(items.size());
     c->graphs4.clear();
+    return MRT_OK;
+}
+
+int build_items_pipe(mrt_ctx* c, const PipeShape& shape) {
+    std::string& ctx_err = c->err;
+    std::vector<Item> items;
+    add_items(items, 0, c->nx, c->ny, shape.rows, mrt::pipe_width(shape.waves));
+    if (c->d_items_p) HIPTRY(hipFree(c->d_items_p));
+    c->d_items_p = nullptr;
+    HIPTRY(hipMalloc(&c->d_items_p, items.size() * sizeof(Item)));
+    HIPTRY(hipMemcpy(c->d_items_p, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
+    c->nitems_p = int(items.size());
+    c->rows_p = shape.rows;
+    c->waves_p = shape.waves;
+    c->graphs_p.clear();
     return MRT_OK;
 }
 
@@ -623,6 +702,12 @@ int mrt_init_grid(mrt_ctx** out, int nx, int ny, int precision, const int bc[4],
     if (tube_inst_ok(c->inst)) {
         if (build_items4(c) != MRT_OK) return fail(MRT_EDEVICE);
         c->per_pass = kTubeSteps;
+    } else {
+        const PipeShape shape = pipe_shape(nx, ny, precision, 0);
+        if (pipe_default(nx, ny, precision, c->per_pass, shape)) {
+            if (build_items_pipe(c, shape) != MRT_OK) return fail(MRT_EDEVICE);
+            c->pipe = true;
+        }
     }
     (void)ctx_err;
     *out = c;
@@ -694,6 +779,39 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
     if (!c->params_set || !c->fields_set) return ctx_fail(c, MRT_ESTATE, "params and fields must be set");
     const int perim = 2 * (c->nx + c->ny);
     const bool reflect = has_kind(c->bc, MRT_BC_REFLECT);
+    const bool xwall = c->bc[0] == MRT_BC_REFLECT || c->bc[1] == MRT_BC_REFLECT;
+    if (c->pipe && c->scheme == 0 && n >= kPipeSteps) {
+        // the level pipeline, four steps a pass; the remaining steps by the
+        // forms below.  It forms the y-wall ghosts itself and reads those of
+        // x walls from the ring
+        auto enqueue_p = [&](int cur, hipStream_t st) -> hipError_t {
+            if (xwall) {
+                const hipError_t e = mrt::k_ghost(c->prec, c->d_inst, 1, perim, c->f[cur], 1, st);
+                if (e != hipSuccess) return e;
+            }
+            return mrt::k_pipe(c->prec, c->waves_p, c->d_inst, c->d_items_p, c->nitems_p, c->f[cur], c->f[1 - cur],
+                               c->d_health, c->nt, st);
+        };
+        const int passes = n / kPipeSteps;
+        if (c->eager || passes == 1) {
+            if (launch)
+                for (int k = 0; k < passes; ++k) {
+                    HIPTRY(enqueue_p(c->cur, c->stream));
+                    c->cur ^= 1;
+                }
+        } else {
+            HIPTRY(run_graphs(c->graphs_p, c->cur, passes, c->stream, enqueue_p, launch));
+        }
+        if (launch) c->ghosts_stale = reflect;
+        n -= passes * kPipeSteps;
+        if (n == 0) return MRT_OK;
+    }
+    // the one-step kernel that keeps the wall ghosts itself expects them
+    // current; the other forms refill them
+    if (launch && c->ghosts_stale && c->per_pass == 1 && c->scheme == 0) {
+        HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, perim, c->f[c->cur], 1, c->stream));
+        c->ghosts_stale = false;
+    }
     // one step reading buffer `cur`: reflecting-wall ghosts unless the step
     // kernel wrote them with the previous step's output (c->walls), then the
     // step.  The per-cell nine-point kernel writes none, so its ghosts
@@ -728,7 +846,6 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
         // The two-step kernel writes the reflecting y-wall ghosts of its
         // output, so the ghost pass runs before the first pass of a call or
         // graph only, unless an x side reflects (then before every pass)
-        const bool xwall = c->bc[0] == MRT_BC_REFLECT || c->bc[1] == MRT_BC_REFLECT;
         auto enqueue2 = [&](int cur, hipStream_t st, int k) -> hipError_t {
             if (reflect && (k == 0 || xwall)) {
                 const hipError_t e = mrt::k_ghost(c->prec, c->d_inst, 1, perim, c->f[cur], 1, st);
@@ -902,6 +1019,7 @@ int mrt_set_steps_per_pass(mrt_ctx* c, int steps, int rows) {
         }
     }
     c->per_pass = steps;
+    c->pipe = false;
     c->graphs.clear();
     c->graphs2.clear();
     c->graphs4.clear();
@@ -912,6 +1030,26 @@ int mrt_set_steps_per_pass(mrt_ctx* c, int steps, int rows) {
         if (rc != MRT_OK) return rc;
     }
     HIPTRY(hipStreamSynchronize(c->stream));
+    return MRT_OK;
+}
+
+int mrt_set_pipeline(mrt_ctx* c, int rows) {
+    if (!c) return MRT_EINVAL;
+    if (rows < -1) return ctx_fail(c, MRT_EINVAL, "rows: -1 (off), 0 (default) or a band height");
+    if (rows >= 0) {
+        const PipeShape shape = pipe_shape(c->nx, c->ny, c->prec, std::min(rows, c->ny));
+        if (shape.rows != c->rows_p || shape.waves != c->waves_p || !c->d_items_p) {
+            const int rc = build_items_pipe(c, shape);
+            if (rc != MRT_OK) return rc;
+        }
+    }
+    c->pipe = rows >= 0;
+    return MRT_OK;
+}
+
+int mrt_get_pipeline(const mrt_ctx* c, int* rows) {
+    if (!c) return MRT_EINVAL;
+    if (rows) *rows = c->pipe ? c->rows_p : -1;
     return MRT_OK;
 }
 
@@ -975,6 +1113,7 @@ int mrt_autotune(mrt_ctx* c, int steps) {
     const int row_opts[] = {1, 2, 3, 4, 5, 6, 8, 12, 16, 32, 64, 128};
     const int grid_mult[] = {0, 2, 4, 8};
     c->per_pass = 1;
+    c->pipe = false;
     float best = 1e30f;
     int best_rows = c->rows, best_grid = c->grid;
     for (int r : row_opts) {
@@ -1029,6 +1168,30 @@ int mrt_autotune(mrt_ctx* c, int steps) {
             HIPTRY(hipMemcpyAsync(c->f[c->cur], save, bytes, hipMemcpyDeviceToDevice, c->stream));
         }
     }
+    // the level pipeline, per step (what remains of a step count runs by the
+    // best of the forms above)
+    bool best_pipe = false;
+    if (c->scheme == 0) {
+        if (build_items_pipe(c, pipe_shape(c->nx, c->ny, c->prec, 0)) != MRT_OK) return MRT_EDEVICE;
+        const int steps4 = kPipeSteps * std::max(1, (steps + kPipeSteps - 1) / kPipeSteps);
+        c->pipe = true;
+        c->eager = true;
+        mrt_step(c, kPipeSteps);
+        HIPTRY(hipEventRecord(e0, c->stream));
+        mrt_step(c, steps4);
+        HIPTRY(hipEventRecord(e1, c->stream));
+        c->eager = false;
+        c->pipe = false;
+        HIPTRY(hipEventSynchronize(e1));
+        float ms = 0;
+        HIPTRY(hipEventElapsedTime(&ms, e0, e1));
+        if (ms / float(steps4) < best) {
+            best = ms / float(steps4);
+            best_pipe = true;
+        }
+        c->ghosts_stale = false;     // the saved state has them
+        HIPTRY(hipMemcpyAsync(c->f[c->cur], save, bytes, hipMemcpyDeviceToDevice, c->stream));
+    }
     // the tube march, per step
     if (tube_inst_ok(c->inst) && c->scheme == 0) {
         if (build_items4(c) != MRT_OK) return MRT_EDEVICE;
@@ -1046,6 +1209,7 @@ int mrt_autotune(mrt_ctx* c, int steps) {
         if (ms / float(steps4) < best) {
             best = ms / float(steps4);
             best_pass = kTubeSteps;
+            best_pipe = false;
         }
         HIPTRY(hipMemcpyAsync(c->f[c->cur], save, bytes, hipMemcpyDeviceToDevice, c->stream));
     }
@@ -1054,6 +1218,7 @@ int mrt_autotune(mrt_ctx* c, int steps) {
     HIPTRY(hipEventDestroy(e1));
     HIPTRY(hipFree(save));
     HIPTRY(hipMemsetAsync(c->d_health, 0, sizeof(unsigned), c->stream));
+    c->pipe = best_pipe;
     if (build_items(c, best_rows) != MRT_OK) return MRT_EDEVICE;
     c->grid = best_grid;
     c->per_pass = best_pass;
@@ -1077,10 +1242,12 @@ void mrt_destroy(mrt_ctx* c) {
     if (c->d_items_adj) (void)hipFree(c->d_items_adj);
     if (c->d_items2) (void)hipFree(c->d_items2);
     if (c->d_items4) (void)hipFree(c->d_items4);
+    if (c->d_items_p) (void)hipFree(c->d_items_p);
     if (c->f_tmp) (void)hipFree(c->f_tmp);
     c->graphs.clear();
     c->graphs2.clear();
     c->graphs4.clear();
+    c->graphs_p.clear();
     if (c->d_stage) (void)hipFree(c->d_stage);
     if (c->d_partial) (void)hipFree(c->d_partial);
     if (c->d_health) (void)hipFree(c->d_health);

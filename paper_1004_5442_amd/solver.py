@@ -173,6 +173,17 @@ class Solver:
         self._check(L.raw().mrt_get_steps_per_pass(self._h, byref(k), byref(r)))
         return k.value, r.value
 
+    def set_pipeline(self, rows: int = 0):
+        """Four steps at a time by the level pipeline (mrt_set_pipeline);
+        rows: band height (0: default, -1: off)."""
+        self._check(L.raw().mrt_set_pipeline(self._h, int(rows)))
+
+    def pipeline(self):
+        """Band height of the level pipeline, -1 when it is off."""
+        r = c_int()
+        self._check(L.raw().mrt_get_pipeline(self._h, byref(r)))
+        return r.value
+
     def set_tile(self, rows: int, grid: int = 0):
         self._check(L.raw().mrt_set_tile(self._h, int(rows), int(grid)))
 

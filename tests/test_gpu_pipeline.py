@@ -1,0 +1,110 @@
+"""GPU parity of the level pipeline (mrt_set_pipeline): four steps per launch,
+one group of waves per time level, rows handed on through LDS.
+
+Against the FP64 oracle (the stated 1e-5 on rho, u, T; 1e-12 of the
+population scale in FP64) and against the one-step kernel, which rounds every
+level alike (the increments are the same FMA chains; the FP64 collision's
+fusion may differ per copy of the code): ragged shapes around the blocks' 120
+stored columns, one row, one column, bands from one row to the whole height,
+every boundary kind on every side.
+"""
+import numpy as np
+import pytest
+
+from helpers import field_errors, oracle_run, smooth_case
+from oracle import mrt
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs the GPU", allow_module_level=True)
+
+from paper_1004_5442_amd.solver import solver_for_case  # noqa: E402
+
+BC_SETS = [
+    ("periodic", "periodic", "periodic", "periodic"),
+    ("reflect", "reflect", "reflect", "reflect"),
+    ("eq", "outflow", "reflect", "reflect"),
+    ("reflect", "eq", "periodic", "periodic"),
+    ("outflow", "reflect", "eq", "outflow"),
+    ("periodic", "periodic", "reflect", "eq"),
+]
+# columns around one and two blocks of 120 stored columns, a wall at a block's
+# first and last lanes (116..124), fewer columns or rows than the overlap
+SHAPES = [((150, 37), 8), ((120, 5), 2), ((1, 7), 3), ((65, 1), 1), ((121, 12), 5), ((119, 9), 9),
+          ((124, 3), 1), ((116, 40), 40), ((2, 2), 1), ((241, 4), 4), ((123, 20), 0)]
+
+
+def run_pair(case, prec, rows, nsteps):
+    one = solver_for_case(case, prec)
+    one.set_steps_per_pass(1, 0)
+    one.step(nsteps)
+    pipe = solver_for_case(case, prec)
+    pipe.set_pipeline(rows)
+    assert pipe.pipeline() >= 1
+    pipe.step(nsteps)
+    a, b, fields = pipe.populations(), one.populations(), pipe.moments()
+    one.close()
+    pipe.close()
+    return a, b, fields
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_eq64", "fp32"])
+@pytest.mark.parametrize("bc", BC_SETS)
+@pytest.mark.parametrize("shape,rows", SHAPES)
+def test_pipeline_matches_oracle_and_single_step(shape, rows, bc, prec):
+    nx, ny = shape
+    nsteps = 13                     # three passes and one single step
+    case = smooth_case(nx, ny, bc, seed=3 * nx + ny)
+    print(f"case {case.name} bc={bc} rows={rows} {prec} pipeline", flush=True)
+    want, p = oracle_run(case, nsteps)
+    got, one, fields = run_pair(case, prec, rows, nsteps)
+    scale = np.abs(want).max()
+    d = float(np.max(np.abs(got - one)) / scale)
+    if prec == "fp64":
+        err = float(np.max(np.abs(got - want)) / scale)
+        assert err <= 1e-12 and d <= 1e-13, (err, d)
+    else:
+        err = field_errors(fields, mrt.macroscopic(want, p.b))
+        assert max(err.values()) < 1e-5, err
+        assert d <= (0.0 if prec == "fp32" else 1e-6), d
+
+
+def test_pipeline_graphs_and_switches():
+    """Graph replays, remainders of one to three steps, and switches to the
+    other forms and back: the wall ghosts, which the pipeline does not write,
+    are current for the step kernel that expects them."""
+    case = smooth_case(300, 40, ("reflect", "eq", "reflect", "outflow"), seed=21)
+    print(f"case {case.name} pipeline graphs", flush=True)
+    s = solver_for_case(case, "fp32_eq64")
+    total = 0
+    for n, rows in ((259, 0), (1, 0), (6, 7), (3, -1), (8, 0), (1, -1)):
+        s.set_pipeline(rows)
+        s.step(n)
+        total += n
+    s.set_pipeline(0)
+    s.prepare(12)
+    s.step(12)
+    s.set_steps_per_pass(2, 8)
+    assert s.pipeline() == -1
+    s.step(3)
+    want, p = oracle_run(case, total + 15)
+    err = field_errors(s.moments(), mrt.macroscopic(want, p.b))
+    assert max(err.values()) < 1e-5, err
+    s.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_eq64"])
+def test_pipeline_reports_an_unhealthy_state(prec):
+    from paper_1004_5442_amd.lib import UnstableError
+    case = smooth_case(130, 20, BC_SETS[1], seed=2)
+    s = solver_for_case(case, prec)
+    s.set_pipeline(0)
+    f = s.populations()
+    f[:, 11, 119] = -f[:, 11, 119]          # rho < 0 in a cell of the first block's last column
+    s.set_populations(f)
+    s.step(4)
+    with pytest.raises(UnstableError):
+        s.sync()
+    s.close()
