@@ -947,330 +947,6 @@ __global__ __launch_bounds__(256, (step2_waves<S>())) void step2_kernel(const In
     }
 }
 
-// --------------------------------------------------------- level pipeline
-
-}  // namespace mrt
-
-#include "mrt_pipe.h"
-
-namespace mrt {
-
-// Four time steps per pass.  A block owns 64 WC columns of a band of rows
-// and holds one group of WC waves per time level: the waves of level
-// k read a row of f^{n+k} from LDS, finish the row below it as f^{n+k+1} and
-// hand that to level k + 1 through LDS (level 0's rows are loaded into LDS
-// straight from memory, the last level's go to memory).  Every iteration
-// moves each level up one row; level k + 1 runs two rows behind level k, so
-// one barrier per iteration orders everything (the row buffers alternate
-// between two slots).
-//
-// A wave keeps one row of its input and that row's increment without its
-// north term: when the next row arrives it closes the increment (the north
-// neighbour is the last term of lw_increment's chain, so the rounding is the
-// one of the other step kernels) and starts the new row's.  That is 32 values
-// per lane instead of a four-row window.  The x neighbours are LDS reads one
-// column to either side: no lane shifts and no edge exchange.
-//
-// Columns: lane c covers column x0 - L + c, L = kPipeSteps; level k's input is
-// exact on the lanes k <= c < 64 WC - k and the block stores the
-// pipe_width(WC) columns that are exact after L levels (the next block starts
-// there).  Rows: level k emits rows y0 - (L-1-k) .. y1 + (L-1-k) - 1, clipped
-// at non-periodic sides, the neighbouring bands recomputing the overlap.
-// Boundaries act on every level as on a stored state: periodic sides are
-// computed at the wrapped cells; the ghost rows of the other kinds are formed
-// from the adjacent row when it arrives (ghost_row_rule).  The ghost columns of
-// levels 1 and up belong to the ghost column's lane: for fixed equilibria it
-// writes them once and then leaves them alone; beside outflow and reflecting
-// sides it reads the wall cell's columns, so that it computes the wall cell's
-// value, and writes that or its reflection (a second write by the wall cell's
-// lane made the blocks at the sides half as slow again, and a grid of one
-// round of blocks waits for them).  Level 0 reads x ghosts from the ghost ring
-// and needs no y ghosts.
-//
-// Level 0's rows are loaded two iterations ahead (three slots): one iteration
-// is shorter than a loaded memory's latency, and a block waits for its
-// slowest wave.
-constexpr int kPipeAhead = 2;
-
-template <typename S, int WC>
-struct PipeRows {
-    static constexpr int kCols = 64 * WC;
-    static constexpr int kRow = 16 * kCols + 2;          // one element before and after the 16 sub-rows
-    static constexpr int kSlots = kPipeAhead + 1;        // of level 0; two of each further level
-    S v[kSlots + 2 * (kPipeSteps - 1)][kRow];
-};
-
-// One dword per lane from global memory (a + off) to LDS (lds + 4 lane),
-// without passing through registers; the caller waits with dma_wait().  (M0,
-// which the compiler sets itself before each of its own uses, holds the LDS
-// address.)
-__device__ __forceinline__ void dma_dword(unsigned long long a, unsigned off, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, %0"
-                 :: "s"(a), "v"(off), "s"(lds) : "memory");
-}
-// Waits until at most N of this wave's memory operations are in flight.
-template <int N>
-__device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-
-// Stencil weights, held in vector registers in the pure FP32 form, which has
-// them to spare: an FP32 FMA with vector operands only issues in half the
-// time of one with a scalar operand (1.1 against 1.8 ns per instruction and
-// SIMD; 217 -> 209 us per step at 4096^2).  The other forms read them as
-// scalars: FP64 gained nothing from it, FP32 storage with FP64 collision
-// fills its 128 registers.
-template <typename S, bool HELD>
-struct PipeWeights {
-    S w[2][4][3];        // [axis][shell]: downstream, upstream, their sum
-    __device__ __forceinline__ explicit PipeWeights(ConstInst* P) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                w[a][k][0] = Weights<S>::get(P, a, k, 0);
-                w[a][k][1] = Weights<S>::get(P, a, k, 1);
-                w[a][k][2] = Weights<S>::sum(P, a, k);
-#pragma unroll
-                for (int j = 0; j < 3; ++j) asm volatile("" : "+v"(w[a][k][j]));
-            }
-    }
-    __device__ __forceinline__ S get(ConstInst*, int a, int k, int j) const { return w[a][k][j]; }
-};
-template <typename S>
-struct PipeWeights<S, false> {
-    __device__ __forceinline__ explicit PipeWeights(ConstInst*) {}
-    __device__ __forceinline__ S get(ConstInst* P, int a, int k, int j) const {
-        return j < 2 ? Weights<S>::get(P, a, k, j) : Weights<S>::sum(P, a, k);
-    }
-};
-
-template <typename S, typename C, bool COMP, bool NT, int WC>
-__device__ __forceinline__ void pipe_block(ConstInst* __restrict__ P, int x0, int y0, int y1,
-                                           const S* __restrict__ fin, S* __restrict__ fout,
-                                           unsigned* __restrict__ health, PipeRows<S, WC>& lds) {
-    constexpr int L = kPipeSteps, CW = 64 * WC;
-    constexpr int kRow = PipeRows<S, WC>::kRow, kSlots = PipeRows<S, WC>::kSlots;
-    constexpr int kParts = sizeof(S) / 4;            // dwords per value
-    const int lane = lane_id();
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lev = wid / WC, cw = wid % WC;
-    const int nx = P->nx, ny = P->ny;
-    const int c = 64 * cw + lane, x = x0 - L + c;
-    const C b = C(P->b), binv = C(P->binv);
-    const bool per_x = P->bc[XLO] == BC_PERIODIC;
-    const bool per_lo = P->bc[YLO] == BC_PERIODIC, per_hi = P->bc[YHI] == BC_PERIODIC;
-    const unsigned origin = unsigned(P->origin), pitch = unsigned(P->pitch);
-    const unsigned long long pstep = (unsigned long long)P->plane * sizeof(S);
-    const unsigned long long fib = reinterpret_cast<unsigned long long>(fin + P->off);
-    const unsigned long long fob = reinterpret_cast<unsigned long long>(fout + P->off);
-    // row pointers at column -1, as in step2_block
-    auto row_at = [&](unsigned long long base, int y) {
-        return base + ((unsigned long long)(origin + unsigned(y) * pitch) - 1u) * sizeof(S);
-    };
-
-    // rows this level emits, [e_lo, e_hi), and the first row it reads
-    int e_lo = y0 - (L - 1 - lev), e_hi = y1 + (L - 1 - lev);
-    if (!per_lo && e_lo < 0) e_lo = 0;
-    if (!per_hi && e_hi > ny) e_hi = ny;
-    const int c_lo = !per_lo && e_lo == 0 ? 0 : e_lo - 1;
-    const int rs = y0 - L;
-
-    // Level 0: the row loads, two rows ahead of the row that it reads.  Lane l
-    // of part p of a sub-row moves dword 64 p + l of the wave's 64 columns, each
-    // from where the boundary remap reads it.  (16 bytes per lane, with the
-    // remapped columns patched in afterwards, measured 1 to 9 % slower.)
-    unsigned boff[kParts];
-    const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&lds.v[0][0];
-    const int l_hi = !per_hi && e_hi == ny ? ny - 1 : e_hi;     // last row read from memory
-    int next = rs, src = rs;                                    // next row to load and where it is
-    if (lev == 0) {
-#pragma unroll
-        for (int p = 0; p < kParts; ++p) {
-            const int d = 64 * p + lane;
-            int xc = x0 - L + 64 * cw + d / kParts;
-            if (per_x) {
-                xc %= nx;
-                if (xc < 0) xc += nx;
-            } else {
-                xc = xc < 0 ? P->col_lo : (xc >= nx ? P->col_hi : xc);
-            }
-            boff[p] = unsigned(xc + 1) * unsigned(sizeof(S)) + unsigned(d % kParts) * 4u;
-        }
-        if (per_lo) {
-            src %= ny;
-            if (src < 0) src += ny;
-        }
-    }
-    auto load_next = [&](int slot) -> bool {
-        const bool any = next >= c_lo && next <= l_hi;
-        if (any) {
-            unsigned long long a = row_at(fib, src);
-            unsigned to = lds0 + unsigned((slot * kRow + 1 + 64 * cw) * int(sizeof(S)));
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-#pragma unroll
-                for (int p = 0; p < kParts; ++p) dma_dword(a, boff[p], to + 256u * unsigned(p));
-                a = next_pop(a, pstep);
-                to += unsigned(CW * sizeof(S));
-            }
-        }
-        ++next;
-        ++src;
-        if (per_lo && src == ny) src = 0;
-        return any;
-    };
-    // at most the row issued last may still be in flight
-    auto wait_rows = [&](bool newer) {
-        if (newer)
-            dma_wait<16 * kParts>();
-        else
-            dma_wait<0>();
-    };
-
-    // ghost columns (x = -1, x = nx) of the non-periodic x sides
-    const bool ghost_lo = !per_x && x == -1, ghost_hi = !per_x && x == nx;
-    const int kind_lo = P->bc[XLO], kind_hi = P->bc[XHI];
-    const bool fixed = (ghost_lo && kind_lo == BC_EQ) || (ghost_hi && kind_hi == BC_EQ);
-    const bool mirrored = (ghost_lo && kind_lo == BC_REFLECT) || (ghost_hi && kind_hi == BC_REFLECT);
-    const int xw = x0 - L + 64 * cw;
-    const bool x_mirror = (kind_lo == BC_REFLECT && xw <= -1) || (kind_hi == BC_REFLECT && xw <= nx && xw + 63 >= nx);
-    // column read: the wall cell's for a ghost column that follows it
-    const int cr = !fixed ? (ghost_lo ? c + 1 : (ghost_hi ? c - 1 : c)) : c;
-    if (lev > 0 && fixed) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const S g = S(ghost_lo ? P->ghost[XLO][i] : P->ghost[XHI][i]);
-            lds.v[kSlots + 2 * (lev - 1)][1 + i * CW + c] = g;
-            lds.v[kSlots + 2 * (lev - 1) + 1][1 + i * CW + c] = g;
-        }
-    }
-    const bool valid = c >= lev && c < CW - lev && x >= 0 && x < nx;
-    const bool stored = c >= L && c < CW - L && x < nx;
-    const unsigned bxs = unsigned(x + 1) * unsigned(sizeof(S));
-    bool healthy = true;
-
-    const PipeWeights<S, COMP> W(P);
-    S D[16];
-    // one row: F holds row r - 1 of this level's input (D its increment), v
-    // receives row r
-    int slot0 = 0;                   // level 0's slot of this iteration's row
-    auto body = [&](S (&F)[16], S (&v)[16], int t) {
-        const int r = rs + t - 2 * lev;
-        bool newer = false;          // a row later than the next one is in flight
-        if (lev == 0) newer = load_next(slot0 == 0 ? kSlots - 1 : slot0 - 1);
-        const int at = lev == 0 ? slot0 : kSlots + 2 * (lev - 1) + (t & 1);
-        const S* in = &lds.v[at][1 + cr];
-        if (r >= c_lo && r <= e_hi) {
-            ConstInst* __restrict__ Pc = reload(P);
-            if (r == ny && !per_hi) {
-                ghost_row_rule<S, C>(P, YHI, F, b, binv, v);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) v[i] = in[i * CW];
-            }
-            if (r > e_lo) {              // close and emit row r - 1
-                S o[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    S d = D[i];
-                    if (moves_y(i)) {
-                        const int k = i >> 2;
-                        d = fma_s(W.get(Pc, 1, k, sgn_y(i) > 0 ? 0 : 1), v[i], d);
-                    }
-                    o[i] = F[i] + d;
-                }
-                if (lev == L - 1) {
-                    if (stored) {
-                        unsigned long long a = row_at(fob, r - 1);
-                        const unsigned bo = lane_off(bxs);
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            gstore<S, NT>(a, bo, o[i]);
-                            if (i < 15) a = next_pop(a, pstep);
-                        }
-                    }
-                } else {
-                    S* out = &lds.v[kSlots + 2 * lev + ((t + 1) & 1)][1 + c];
-                    if (x_mirror) {
-                        S g[16];
-                        reflected_eq<C>(o, 0, b, binv, g);
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) o[i] = mirrored ? g[i] : o[i];
-                    }
-                    if (!fixed) {
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) out[i * CW] = o[i];
-                    }
-                }
-            }
-            if (r >= e_lo && r < e_hi) {     // row r's increment but for its north term
-                if (r == 0 && !per_lo) ghost_row_rule<S, C>(P, YLO, v, b, binv, F);
-                S cdt[16];
-                C rho, Pp;
-                cell_collision<C, COMP>(v, b, binv, Pc->sdt, cdt, rho, Pp);
-                healthy = healthy && (!valid || (rho > C(0) && Pp > C(0)));
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int k = i >> 2, sx = sgn_x(i), sy = sgn_y(i);
-                    S d = -cdt[i];
-                    if (sx != 0) {
-                        d = fma_s(-W.get(Pc, 0, k, 2), v[i], d);
-                        d = fma_s(W.get(Pc, 0, k, sx > 0 ? 1 : 0), in[i * CW - 1], d);
-                        d = fma_s(W.get(Pc, 0, k, sx > 0 ? 0 : 1), in[i * CW + 1], d);
-                    }
-                    if (sy != 0) {
-                        d = fma_s(-W.get(Pc, 1, k, 2), v[i], d);
-                        d = fma_s(W.get(Pc, 1, k, sy > 0 ? 1 : 0), F[i], d);
-                    }
-                    D[i] = d;
-                }
-            }
-        }
-        if (lev == 0) {
-            wait_rows(newer);
-            slot0 = slot0 == kSlots - 1 ? 0 : slot0 + 1;
-        }
-        __syncthreads();
-    };
-
-    S A[16], B[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) A[i] = B[i] = D[i] = S(0);
-    static_assert(kPipeAhead == 2, "two rows before the march");
-    if (lev == 0) {
-        load_next(0);
-        wait_rows(load_next(1));
-    }
-    __syncthreads();
-    const int last = y1 - rs + 2 * (L - 1);      // the last level reads row y1
-    for (int t = 0; t <= last;) {
-        body(A, B, t); ++t;
-        if (t > last) break;
-        body(B, A, t); ++t;
-    }
-    if (!healthy) atomicOr(health, 1u);
-}
-
-// Sixteen waves per CU in FP32 storage (four per SIMD, 128 VGPRs; two blocks
-// with two waves per level or one with four, 148 KB of LDS), eight in FP64
-// (two per SIMD, one block with two waves per level, 148 KB).
-template <typename S>
-constexpr int pipe_occupancy() { return sizeof(S) == 4 ? 4 : 2; }
-
-template <typename S, typename C, bool COMP, bool NT, int WC>
-__global__ __launch_bounds__(64 * kPipeSteps * WC, (pipe_occupancy<S>())) void pipe_kernel(
-        const Inst* __restrict__ insts, const Item* __restrict__ items, int nitems,
-        const S* __restrict__ fin, S* __restrict__ fout, unsigned* __restrict__ health) {
-    __shared__ PipeRows<S, WC> lds;
-    ConstInst* cinsts = (ConstInst*)insts;
-    ConstItem* citems = (ConstItem*)items;
-    // XCD-aware item order as in step_kernel
-    const int per = (nitems + 7) >> 3;
-    const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if (w >= nitems) return;
-    pipe_block<S, C, COMP, NT, WC>(cinsts + citems[w].inst, citems[w].x0, citems[w].y0, citems[w].y1, fin,
-                               fout, health, lds);
-}
-
 // ---------------------------------------------------------------- adjoint
 
 // Adjoint of one step on a periodic grid (neighbours wrap through the
@@ -1709,6 +1385,330 @@ __global__ __launch_bounds__(256, (tube_waves<S, NY>())) void tube_kernel(
         tube_block<S, C, COMP, NT, L, NY>(cinsts + citems[w].inst, citems[w].x0, fin, fout, health, lds);
         __syncthreads();   // the next item reuses the LDS buffers
     }
+}
+
+// --------------------------------------------------------- level pipeline
+
+}  // namespace mrt
+
+#include "mrt_pipe.h"
+
+namespace mrt {
+
+// Four time steps per pass.  A block owns 64 WC columns of a band of rows
+// and holds one group of WC waves per time level: the waves of level
+// k read a row of f^{n+k} from LDS, finish the row below it as f^{n+k+1} and
+// hand that to level k + 1 through LDS (level 0's rows are loaded into LDS
+// straight from memory, the last level's go to memory).  Every iteration
+// moves each level up one row; level k + 1 runs two rows behind level k, so
+// one barrier per iteration orders everything (the row buffers alternate
+// between two slots).
+//
+// A wave keeps one row of its input and that row's increment without its
+// north term: when the next row arrives it closes the increment (the north
+// neighbour is the last term of lw_increment's chain, so the rounding is the
+// one of the other step kernels) and starts the new row's.  That is 32 values
+// per lane instead of a four-row window.  The x neighbours are LDS reads one
+// column to either side: no lane shifts and no edge exchange.
+//
+// Columns: lane c covers column x0 - L + c, L = kPipeSteps; level k's input is
+// exact on the lanes k <= c < 64 WC - k and the block stores the
+// pipe_width(WC) columns that are exact after L levels (the next block starts
+// there).  Rows: level k emits rows y0 - (L-1-k) .. y1 + (L-1-k) - 1, clipped
+// at non-periodic sides, the neighbouring bands recomputing the overlap.
+// Boundaries act on every level as on a stored state: periodic sides are
+// computed at the wrapped cells; the ghost rows of the other kinds are formed
+// from the adjacent row when it arrives (ghost_row_rule).  The ghost columns of
+// levels 1 and up belong to the ghost column's lane: for fixed equilibria it
+// writes them once and then leaves them alone; beside outflow and reflecting
+// sides it reads the wall cell's columns, so that it computes the wall cell's
+// value, and writes that or its reflection (a second write by the wall cell's
+// lane made the blocks at the sides half as slow again, and a grid of one
+// round of blocks waits for them).  Level 0 reads x ghosts from the ghost ring
+// and needs no y ghosts.
+//
+// Level 0's rows are loaded two iterations ahead (three slots): one iteration
+// is shorter than a loaded memory's latency, and a block waits for its
+// slowest wave.
+constexpr int kPipeAhead = 2;
+
+template <typename S, int WC>
+struct PipeRows {
+    static constexpr int kCols = 64 * WC;
+    static constexpr int kRow = 16 * kCols + 2;          // one element before and after the 16 sub-rows
+    static constexpr int kSlots = kPipeAhead + 1;        // of level 0; two of each further level
+    S v[kSlots + 2 * (kPipeSteps - 1)][kRow];
+};
+
+// One dword per lane from global memory (a + off) to LDS (lds + 4 lane),
+// without passing through registers; the caller waits with dma_wait().  (M0,
+// which the compiler sets itself before each of its own uses, holds the LDS
+// address.)
+__device__ __forceinline__ void dma_dword(unsigned long long a, unsigned off, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, %0"
+                 :: "s"(a), "v"(off), "s"(lds) : "memory");
+}
+// Waits until at most N of this wave's memory operations are in flight.
+template <int N>
+__device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+
+// Stencil weights, held in vector registers in the pure FP32 form, which has
+// them to spare: an FP32 FMA with vector operands only issues in half the
+// time of one with a scalar operand (1.1 against 1.8 ns per instruction and
+// SIMD; 217 -> 209 us per step at 4096^2).  The other forms read them as
+// scalars: FP64 gained nothing from it, FP32 storage with FP64 collision
+// fills its 128 registers.
+template <typename S, bool HELD>
+struct PipeWeights {
+    S w[2][4][3];        // [axis][shell]: downstream, upstream, their sum
+    __device__ __forceinline__ explicit PipeWeights(ConstInst* P) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                w[a][k][0] = Weights<S>::get(P, a, k, 0);
+                w[a][k][1] = Weights<S>::get(P, a, k, 1);
+                w[a][k][2] = Weights<S>::sum(P, a, k);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) asm volatile("" : "+v"(w[a][k][j]));
+            }
+    }
+    __device__ __forceinline__ S get(ConstInst*, int a, int k, int j) const { return w[a][k][j]; }
+};
+template <typename S>
+struct PipeWeights<S, false> {
+    __device__ __forceinline__ explicit PipeWeights(ConstInst*) {}
+    __device__ __forceinline__ S get(ConstInst* P, int a, int k, int j) const {
+        return j < 2 ? Weights<S>::get(P, a, k, j) : Weights<S>::sum(P, a, k);
+    }
+};
+
+template <typename S, typename C, bool COMP, bool NT, int WC>
+__device__ __forceinline__ void pipe_block(ConstInst* __restrict__ P, int x0, int y0, int y1,
+                                           const S* __restrict__ fin, S* __restrict__ fout,
+                                           unsigned* __restrict__ health, PipeRows<S, WC>& lds) {
+    constexpr int L = kPipeSteps, CW = 64 * WC;
+    constexpr int kRow = PipeRows<S, WC>::kRow, kSlots = PipeRows<S, WC>::kSlots;
+    constexpr int kParts = sizeof(S) / 4;            // dwords per value
+    const int lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lev = wid / WC, cw = wid % WC;
+    const int nx = P->nx, ny = P->ny;
+    const int c = 64 * cw + lane, x = x0 - L + c;
+    const C b = C(P->b), binv = C(P->binv);
+    const bool per_x = P->bc[XLO] == BC_PERIODIC;
+    const bool per_lo = P->bc[YLO] == BC_PERIODIC, per_hi = P->bc[YHI] == BC_PERIODIC;
+    const unsigned origin = unsigned(P->origin), pitch = unsigned(P->pitch);
+    const unsigned long long pstep = (unsigned long long)P->plane * sizeof(S);
+    const unsigned long long fib = reinterpret_cast<unsigned long long>(fin + P->off);
+    const unsigned long long fob = reinterpret_cast<unsigned long long>(fout + P->off);
+    // row pointers at column -1, as in step2_block
+    auto row_at = [&](unsigned long long base, int y) {
+        return base + ((unsigned long long)(origin + unsigned(y) * pitch) - 1u) * sizeof(S);
+    };
+
+    // rows this level emits, [e_lo, e_hi), and the first row it reads
+    int e_lo = y0 - (L - 1 - lev), e_hi = y1 + (L - 1 - lev);
+    if (!per_lo && e_lo < 0) e_lo = 0;
+    if (!per_hi && e_hi > ny) e_hi = ny;
+    const int c_lo = !per_lo && e_lo == 0 ? 0 : e_lo - 1;
+    const int rs = y0 - L;
+
+    // Level 0: the row loads, two rows ahead of the row that it reads.  Lane l
+    // of part p of a sub-row moves dword 64 p + l of the wave's 64 columns, each
+    // from where the boundary remap reads it.  (16 bytes per lane, with the
+    // remapped columns patched in afterwards, measured 1 to 9 % slower.)
+    unsigned boff[kParts];
+    const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&lds.v[0][0];
+    const int l_hi = !per_hi && e_hi == ny ? ny - 1 : e_hi;     // last row read from memory
+    int next = rs, src = rs;                                    // next row to load and where it is
+    if (lev == 0) {
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+            const int d = 64 * p + lane;
+            int xc = x0 - L + 64 * cw + d / kParts;
+            if (per_x) {
+                xc %= nx;
+                if (xc < 0) xc += nx;
+            } else {
+                xc = xc < 0 ? P->col_lo : (xc >= nx ? P->col_hi : xc);
+            }
+            boff[p] = unsigned(xc + 1) * unsigned(sizeof(S)) + unsigned(d % kParts) * 4u;
+        }
+        if (per_lo) {
+            src %= ny;
+            if (src < 0) src += ny;
+        }
+    }
+    auto load_next = [&](int slot) -> bool {
+        const bool any = next >= c_lo && next <= l_hi;
+        if (any) {
+            unsigned long long a = row_at(fib, src);
+            unsigned to = lds0 + unsigned((slot * kRow + 1 + 64 * cw) * int(sizeof(S)));
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+#pragma unroll
+                for (int p = 0; p < kParts; ++p) dma_dword(a, boff[p], to + 256u * unsigned(p));
+                a = next_pop(a, pstep);
+                to += unsigned(CW * sizeof(S));
+            }
+        }
+        ++next;
+        ++src;
+        if (per_lo && src == ny) src = 0;
+        return any;
+    };
+    // at most the row issued last may still be in flight
+    auto wait_rows = [&](bool newer) {
+        if (newer)
+            dma_wait<16 * kParts>();
+        else
+            dma_wait<0>();
+    };
+
+    // ghost columns (x = -1, x = nx) of the non-periodic x sides
+    const bool ghost_lo = !per_x && x == -1, ghost_hi = !per_x && x == nx;
+    const int kind_lo = P->bc[XLO], kind_hi = P->bc[XHI];
+    const bool fixed = (ghost_lo && kind_lo == BC_EQ) || (ghost_hi && kind_hi == BC_EQ);
+    const bool mirrored = (ghost_lo && kind_lo == BC_REFLECT) || (ghost_hi && kind_hi == BC_REFLECT);
+    const int xw = x0 - L + 64 * cw;
+    const bool x_mirror = (kind_lo == BC_REFLECT && xw <= -1) || (kind_hi == BC_REFLECT && xw <= nx && xw + 63 >= nx);
+    // column read: the wall cell's for a ghost column that follows it
+    const int cr = !fixed ? (ghost_lo ? c + 1 : (ghost_hi ? c - 1 : c)) : c;
+    if (lev > 0 && fixed) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const S g = S(ghost_lo ? P->ghost[XLO][i] : P->ghost[XHI][i]);
+            lds.v[kSlots + 2 * (lev - 1)][1 + i * CW + c] = g;
+            lds.v[kSlots + 2 * (lev - 1) + 1][1 + i * CW + c] = g;
+        }
+    }
+    const bool valid = c >= lev && c < CW - lev && x >= 0 && x < nx;
+    const bool stored = c >= L && c < CW - L && x < nx;
+    const unsigned bxs = unsigned(x + 1) * unsigned(sizeof(S));
+    bool healthy = true;
+
+    const PipeWeights<S, COMP> W(P);
+    S D[16];
+    // one row: F holds row r - 1 of this level's input (D its increment), v
+    // receives row r
+    int slot0 = 0;                   // level 0's slot of this iteration's row
+    auto body = [&](S (&F)[16], S (&v)[16], int t) {
+        const int r = rs + t - 2 * lev;
+        bool newer = false;          // a row later than the next one is in flight
+        if (lev == 0) newer = load_next(slot0 == 0 ? kSlots - 1 : slot0 - 1);
+        const int at = lev == 0 ? slot0 : kSlots + 2 * (lev - 1) + (t & 1);
+        const S* in = &lds.v[at][1 + cr];
+        if (r >= c_lo && r <= e_hi) {
+            ConstInst* __restrict__ Pc = reload(P);
+            if (r == ny && !per_hi) {
+                ghost_row_rule<S, C>(P, YHI, F, b, binv, v);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = in[i * CW];
+            }
+            if (r > e_lo) {              // close and emit row r - 1
+                S o[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    S d = D[i];
+                    if (moves_y(i)) {
+                        const int k = i >> 2;
+                        d = fma_s(W.get(Pc, 1, k, sgn_y(i) > 0 ? 0 : 1), v[i], d);
+                    }
+                    o[i] = F[i] + d;
+                }
+                if (lev == L - 1) {
+                    if (stored) {
+                        unsigned long long a = row_at(fob, r - 1);
+                        const unsigned bo = lane_off(bxs);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            gstore<S, NT>(a, bo, o[i]);
+                            if (i < 15) a = next_pop(a, pstep);
+                        }
+                    }
+                } else {
+                    S* out = &lds.v[kSlots + 2 * lev + ((t + 1) & 1)][1 + c];
+                    if (x_mirror) {
+                        S g[16];
+                        reflected_eq<C>(o, 0, b, binv, g);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o[i] = mirrored ? g[i] : o[i];
+                    }
+                    if (!fixed) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) out[i * CW] = o[i];
+                    }
+                }
+            }
+            if (r >= e_lo && r < e_hi) {     // row r's increment but for its north term
+                if (r == 0 && !per_lo) ghost_row_rule<S, C>(P, YLO, v, b, binv, F);
+                S cdt[16];
+                C rho, Pp;
+                cell_collision<C, COMP>(v, b, binv, Pc->sdt, cdt, rho, Pp);
+                healthy = healthy && (!valid || (rho > C(0) && Pp > C(0)));
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int k = i >> 2, sx = sgn_x(i), sy = sgn_y(i);
+                    S d = -cdt[i];
+                    if (sx != 0) {
+                        d = fma_s(-W.get(Pc, 0, k, 2), v[i], d);
+                        d = fma_s(W.get(Pc, 0, k, sx > 0 ? 1 : 0), in[i * CW - 1], d);
+                        d = fma_s(W.get(Pc, 0, k, sx > 0 ? 0 : 1), in[i * CW + 1], d);
+                    }
+                    if (sy != 0) {
+                        d = fma_s(-W.get(Pc, 1, k, 2), v[i], d);
+                        d = fma_s(W.get(Pc, 1, k, sy > 0 ? 1 : 0), F[i], d);
+                    }
+                    D[i] = d;
+                }
+            }
+        }
+        if (lev == 0) {
+            wait_rows(newer);
+            slot0 = slot0 == kSlots - 1 ? 0 : slot0 + 1;
+        }
+        __syncthreads();
+    };
+
+    S A[16], B[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) A[i] = B[i] = D[i] = S(0);
+    static_assert(kPipeAhead == 2, "two rows before the march");
+    if (lev == 0) {
+        load_next(0);
+        wait_rows(load_next(1));
+    }
+    __syncthreads();
+    const int last = y1 - rs + 2 * (L - 1);      // the last level reads row y1
+    for (int t = 0; t <= last;) {
+        body(A, B, t); ++t;
+        if (t > last) break;
+        body(B, A, t); ++t;
+    }
+    if (!healthy) atomicOr(health, 1u);
+}
+
+// Sixteen waves per CU in FP32 storage (four per SIMD, 128 VGPRs; two blocks
+// with two waves per level or one with four, 148 KB of LDS), eight in FP64
+// (two per SIMD, one block with two waves per level, 148 KB).
+template <typename S>
+constexpr int pipe_occupancy() { return sizeof(S) == 4 ? 4 : 2; }
+
+template <typename S, typename C, bool COMP, bool NT, int WC>
+__global__ __launch_bounds__(64 * kPipeSteps * WC, (pipe_occupancy<S>())) void pipe_kernel(
+        const Inst* __restrict__ insts, const Item* __restrict__ items, int nitems,
+        const S* __restrict__ fin, S* __restrict__ fout, unsigned* __restrict__ health) {
+    __shared__ PipeRows<S, WC> lds;
+    ConstInst* cinsts = (ConstInst*)insts;
+    ConstItem* citems = (ConstItem*)items;
+    // XCD-aware item order as in step_kernel
+    const int per = (nitems + 7) >> 3;
+    const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (w >= nitems) return;
+    pipe_block<S, C, COMP, NT, WC>(cinsts + citems[w].inst, citems[w].x0, citems[w].y0, citems[w].y1, fin,
+                               fout, health, lds);
 }
 
 // ------------------------------------------------- scheme variants
