@@ -199,10 +199,10 @@ int mrt_get_tile(const mrt_ctx* ctx, int* rows_per_item, int* grid_blocks);
  * pass).
  * steps = 4, the tube march: for grids of 1, 2 or 4 rows, periodic in y,
  * with fixed-equilibrium x sides (the shock tubes of section (b)): one
- * launch advances four steps of Eq. 3, each block holding all rows of 256
- * columns in registers and storing the 248 that are exact after four steps
- * (the overlap is recomputed); rows is ignored; steps beyond a multiple of
- * four run one by one.  Results equal single steps to rounding order
+ * launch advances four or more steps of Eq. 3 (chosen from the grid; what
+ * remains of a step count takes one shorter launch), each block holding all
+ * rows of 64, 128 or 256 columns and storing those that are exact after its
+ * steps (the overlap is recomputed); rows is ignored.  Results equal single steps to rounding order
  * (measured bit-identical in the FP32 storage forms).  mrt_autotune times it
  * too on such grids.  Synchronises.
  * Errors: MRT_EINVAL (steps not 1, 2 or 4; rows out of range; 4 on another

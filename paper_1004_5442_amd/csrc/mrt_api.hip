@@ -29,8 +29,8 @@ hipError_t k_step(int prec, const Inst* insts, const Item* items, int nitems, co
                   void* fout, unsigned* health, int grid, bool nt, bool walls, hipStream_t st);
 hipError_t k_step2(int prec, const Inst* insts, const Item* items, int nitems, const void* fin,
                    void* fout, unsigned* health, int grid, bool nt, bool wrap4, hipStream_t st);
-hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, const void* fin,
-                  void* fout, unsigned* health, int grid, bool nt, int ny, hipStream_t st);
+hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, int waves, int overlap,
+                  int steps, const void* fin, void* fout, unsigned* health, bool nt, int ny, hipStream_t st);
 hipError_t k_pipe(int prec, int waves, const Inst* insts, const Item* items, int nitems, const void* fin,
                   void* fout, unsigned* health, bool nt, hipStream_t st);
 hipError_t k_variant(int prec, const Inst* P, int nx, int ny, int scheme, bool reflect,
@@ -59,7 +59,7 @@ using mrt::Inst;
 using mrt::Item;
 using mrt::kPipeSteps;
 using mrt::kTubeSteps;
-using mrt::kTubeWidth;
+using mrt::kTubeMaxSteps;
 
 // Scratch of mrt_adjoint_step_noalloc: the rate-gradient partial rows of one
 // adjoint step (one row of 16 doubles per work item, then the reduction's 64
@@ -409,6 +409,43 @@ bool pipe_default(int nx, int ny, int prec, int per_pass, const PipeShape& shape
     return shape.cost * iteration[prec] / kPipeSteps < other;
 }
 
+// Launch shape of the tube march: waves per row (a block holds 64 x waves
+// columns of every row) and steps per launch, which is the overlap that a
+// block recomputes on either side.  A launch costs its start, per level the
+// longer of one wave's chain of dependent instructions (a few blocks: the chip
+// is idle but for them) and the waves' throughput, and what of the state's way
+// through memory it does not cover; the shape with the shortest time per step
+// wins.  Small tubes take one wave and long launches (400 x 4 in FP64: 24
+// steps, 1.46 us per step; 8 steps 1.9), large batches four to eight waves a
+// block and eight steps (512 tubes of four rows, FP32 with FP64 collision, us
+// per step: 2 waves x 8 steps 47.1, 2 x 4 49.1, 2 x 12 48.8, 1 x 8 48.9, 4 x 8,
+// sixteen waves in step, 66; FP64 2 x 8 59.2, 2 x 12 60.8, 1 x 8 60.0).
+struct TubeShape {
+    int waves = 1, steps = kTubeSteps;
+};
+TubeShape tube_shape(const std::vector<int>& nx, int ny, int prec) {
+    const bool fp64 = prec == MRT_FP64;
+    const double start = 4.0, chain = 1.2, wave = fp64 ? 0.7 : 0.58;   // us
+    double cells = 0;
+    for (int n : nx) cells += double(n) * ny;
+    const double memory = 0.35 * cells * 32 * (fp64 ? 8 : 4) / 4.5e6;
+    TubeShape best;
+    double best_us = -1;
+    for (int waves : {1, ny == 1 ? 4 : 2})
+        for (int steps = kTubeSteps; steps <= kTubeMaxSteps; steps += 4) {
+            const int width = mrt::tube_width(waves, steps);
+            double blocks = 0;
+            for (int n : nx) blocks += (n + width - 1) / width;
+            const double level = std::max(chain, blocks * ny * waves / 1024.0 * wave);
+            const double us = (start + steps * level + memory) / steps;
+            if (best_us < 0 || us < best_us) {
+                best_us = us;
+                best = TubeShape{waves, steps};
+            }
+        }
+    return best;
+}
+
 // Band height of the batch's two-step kernel when none is given.
 constexpr int kBatchRows2 = 32;
 
@@ -452,6 +489,7 @@ struct mrt_ctx {
     GraphCache graphs2;              // captured two-step passes
     Item* d_items4 = nullptr;        // work items of the tube march
     int nitems4 = 0;
+    TubeShape tube;
     GraphCache graphs4;              // captured tube-march passes
     bool pipe = false;               // four steps at a time by the level pipeline
     Item* d_items_p = nullptr;       // its work items
@@ -546,15 +584,16 @@ bool tube_inst_ok(const Inst& I) {
            I.bc[3] == MRT_BC_PERIODIC && I.bc[0] == MRT_BC_EQ && I.bc[1] == MRT_BC_EQ;
 }
 
-// Tube-march work items of an instance: kTubeWidth-column chunks.
-void add_tube_items(std::vector<Item>& items, int inst, int nx, int ny) {
-    for (int x0 = 0; x0 < nx; x0 += kTubeWidth) items.push_back(Item{inst, x0, 0, ny});
+// Tube-march work items of an instance: as wide as a block stores.
+void add_tube_items(std::vector<Item>& items, int inst, int nx, int ny, const TubeShape& shape) {
+    add_items(items, inst, nx, ny, ny, mrt::tube_width(shape.waves, shape.steps));
 }
 
 int build_items4(mrt_ctx* c) {
     std::string& ctx_err = c->err;
     std::vector<Item> items;
-    add_tube_items(items, 0, c->nx, c->ny);
+    c->tube = tube_shape({c->nx}, c->ny, c->prec);
+    add_tube_items(items, 0, c->nx, c->ny, c->tube);
     if (c->d_items4) HIPTRY(hipFree(c->d_items4));
     c->d_items4 = nullptr;
     HIPTRY(hipMalloc(&c->d_items4, items.size() * sizeof(Item)));
@@ -818,12 +857,14 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
     // (corners too) are always refilled (the split scheme refills those of
     // its post-collision state itself)
     if (c->per_pass == kTubeSteps && c->scheme == 0) {
-        // the tube march (no reflecting sides), the remaining steps one by one
-        auto enqueue4 = [&](int cur, hipStream_t st) -> hipError_t {
-            return mrt::k_tube(c->prec, c->d_inst, c->d_items4, c->nitems4, c->f[cur], c->f[1 - cur],
-                               c->d_health, 0, c->nt, c->ny, st);
+        // the tube march (no reflecting sides): launches of tube.steps steps,
+        // then one of the remaining steps
+        auto march = [&](int cur, hipStream_t st, int steps) -> hipError_t {
+            return mrt::k_tube(c->prec, c->d_inst, c->d_items4, c->nitems4, c->tube.waves, c->tube.steps,
+                               steps, c->f[cur], c->f[1 - cur], c->d_health, c->nt, c->ny, st);
         };
-        const int passes = n / kTubeSteps;
+        auto enqueue4 = [&](int cur, hipStream_t st) -> hipError_t { return march(cur, st, c->tube.steps); };
+        const int passes = n / c->tube.steps, rest = n % c->tube.steps;
         if (c->eager || passes == 1) {
             if (launch)
                 for (int k = 0; k < passes; ++k) {
@@ -833,12 +874,10 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
         } else if (passes > 1) {
             HIPTRY(run_graphs(c->graphs4, c->cur, passes, c->stream, enqueue4, launch));
         }
-        if (launch)
-            for (int k = 0; k < n % kTubeSteps; ++k) {
-                HIPTRY(mrt::k_step(c->prec, c->d_inst, c->d_items, c->nitems, c->f[c->cur], c->f[1 - c->cur],
-                                   c->d_health, c->grid, c->nt, c->walls, c->stream));
-                c->cur ^= 1;
-            }
+        if (launch && rest) {
+            HIPTRY(march(c->cur, c->stream, rest));
+            c->cur ^= 1;
+        }
         return MRT_OK;
     }
     if (c->per_pass == 2 && c->scheme == 0) {
@@ -1196,9 +1235,9 @@ int mrt_autotune(mrt_ctx* c, int steps) {
     if (tube_inst_ok(c->inst) && c->scheme == 0) {
         if (build_items4(c) != MRT_OK) return MRT_EDEVICE;
         c->per_pass = kTubeSteps;
-        const int steps4 = kTubeSteps * std::max(1, (steps + kTubeSteps - 1) / kTubeSteps);
+        const int steps4 = c->tube.steps * std::max(1, (steps + c->tube.steps - 1) / c->tube.steps);
         c->eager = true;
-        mrt_step(c, kTubeSteps);
+        mrt_step(c, c->tube.steps);
         HIPTRY(hipEventRecord(e0, c->stream));
         mrt_step(c, steps4);
         HIPTRY(hipEventRecord(e1, c->stream));
@@ -1523,6 +1562,7 @@ struct mrt_batch {
     GraphCache graphs2;                     // captured two-step passes
     Item* d_items4 = nullptr;               // work items of the tube march
     int nitems4 = 0, tube_ny = 0;           // tube_ny: the rows of every instance
+    TubeShape tube;
     GraphCache graphs4;                     // captured tube-march passes
     std::string err;
 };
@@ -1574,11 +1614,14 @@ bool tube_march_ok(const mrt_batch* b) {
     return true;
 }
 
-// Work items of the tube march: kTubeWidth-column chunks of each instance.
+// Work items of the tube march over every instance.
 int batch_items4(mrt_batch* b) {
     std::string& ctx_err = b->err;
     std::vector<Item> items;
-    for (int i = 0; i < b->count; ++i) add_tube_items(items, i, b->insts[i].nx, b->insts[i].ny);
+    std::vector<int> nx;
+    for (const Inst& I : b->insts) nx.push_back(I.nx);
+    b->tube = tube_shape(nx, b->insts[0].ny, b->prec);
+    for (int i = 0; i < b->count; ++i) add_tube_items(items, i, b->insts[i].nx, b->insts[i].ny, b->tube);
     b->tube_ny = b->insts[0].ny;
     if (b->d_items4) HIPTRY(hipFree(b->d_items4));
     b->d_items4 = nullptr;
@@ -1705,19 +1748,18 @@ static int batch_step_impl(mrt_batch* b, int n, bool launch) {
     if (n == 0) return MRT_OK;
     if (b->per_pass == kTubeSteps) {
         // the tube march (no reflecting sides: its x sides are fixed
-        // equilibria, its y sides periodic), the remaining steps one by one
-        auto enqueue4 = [&](int cur, hipStream_t st) -> hipError_t {
-            return mrt::k_tube(b->prec, b->d_insts, b->d_items4, b->nitems4, b->f[cur], b->f[1 - cur],
-                               b->d_health, 0, b->nt, b->tube_ny, st);
+        // equilibria, its y sides periodic): launches of tube.steps steps,
+        // then one of the remaining steps
+        auto march = [&](int cur, hipStream_t st, int steps) -> hipError_t {
+            return mrt::k_tube(b->prec, b->d_insts, b->d_items4, b->nitems4, b->tube.waves, b->tube.steps,
+                               steps, b->f[cur], b->f[1 - cur], b->d_health, b->nt, b->tube_ny, st);
         };
-        const int passes = n / kTubeSteps;
+        auto enqueue4 = [&](int cur, hipStream_t st) -> hipError_t { return march(cur, st, b->tube.steps); };
+        const int passes = n / b->tube.steps, rest = n % b->tube.steps;
         if (passes > 0) HIPTRY(run_graphs(b->graphs4, b->cur, passes, b->stream, enqueue4, launch));
-        if (launch) {
-            for (int k = 0; k < n % kTubeSteps; ++k) {
-                HIPTRY(mrt::k_step(b->prec, b->d_insts, b->d_items, b->nitems, b->f[b->cur],
-                                   b->f[1 - b->cur], b->d_health, b->grid, b->nt, false, b->stream));
-                b->cur ^= 1;
-            }
+        if (launch && rest) {
+            HIPTRY(march(b->cur, b->stream, rest));
+            b->cur ^= 1;
         }
         return MRT_OK;
     }
@@ -1931,7 +1973,7 @@ int mrt_batch_autotune(mrt_batch* b, int steps) {
     if (tube_march_ok(b)) {
         if (batch_items4(b) != MRT_OK) return MRT_EDEVICE;
         b->per_pass = kTubeSteps;
-        const int steps4 = kTubeSteps * std::max(1, (steps + kTubeSteps - 1) / kTubeSteps);
+        const int steps4 = b->tube.steps * std::max(1, (steps + b->tube.steps - 1) / b->tube.steps);
         mrt_batch_step(b, steps4);    // capture + warm-up
         HIPTRY(hipEventRecord(e0, b->stream));
         mrt_batch_step(b, steps4);

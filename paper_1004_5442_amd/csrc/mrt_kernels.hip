@@ -1230,161 +1230,134 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_partials(const double* 
 namespace mrt {
 
 // Several time steps per pass for grids of NY = 1, 2 or 4 periodic rows
-// whose x sides hold fixed equilibria (the shock tubes of section (b)).  All
-// rows of a tube sit in the registers of one block, so the block can
-// advance them L steps before it stores: level k + 1 of row r is the
-// single-step update of rows r - 1, r, r + 1 (mod NY) of level k.  A block
-// covers the 256 columns x0 - L .. x0 + 255 - L (lane l = 64 w + lane at
-// x0 - L + l); level k is exact on the lanes k <= l <= 255 - k, since each
-// level needs one more column on either side, so a block stores f^{n+L} of
-// the 256 - 2L columns x0 .. x0 + 255 - 2L and the tube's next block starts
-// there (the overlap is recomputed: 2L of 256 lanes; L = kTubeSteps,
-// kTubeWidth stored columns).  No column outside the block is needed: the
-// halo-column computation of the two-step march disappears.  The ghost
-// columns x = -1 and x = nx keep their side's equilibrium at every level;
-// lanes further out carry values that reach no stored cell.  Per level the
-// edge lanes of the four waves swap the rows' x-moving populations through
-// LDS (double buffered: one barrier per level).  The state crosses the
-// memory interface once per L steps.
+// whose x sides hold fixed equilibria (the shock tubes of section (b)).  A
+// block holds all rows of 64 WC columns, one wave per row and 64 columns, and
+// advances them `steps` steps before it stores: level k + 1 of row r is the
+// single-step update of rows r - 1, r, r + 1 (mod NY) of level k.  It covers
+// the columns x0 - overlap .. x0 - overlap + 64 WC - 1; level k is exact but
+// for k columns on either side, so with overlap >= steps the columns x0 ..
+// x0 + tube_width(WC, overlap) - 1 are exact after the last, and the tube's next
+// block starts there (the overlap is recomputed).  The ghost columns x = -1 and
+// x = nx keep their side's equilibrium at every level; lanes further out carry
+// values that reach no stored cell.  Per level every wave puts its row into
+// LDS (buffers alternate) and reads its neighbours from there, x ones a column to either side, y ones from the other rows; the
+// collision needs only the wave's own row, so the reads arrive during it.  The
+// state crosses the memory interface once per launch.
+//
+// One wave per row rather than all rows in every lane: the rows' cell updates,
+// a chain of dependent instructions each, run beside each other (on a tube of
+// a few blocks a launch is nothing but that chain), a lane holds one row's
+// values (FP32 storage runs four waves per SIMD instead of two), and the
+// neighbours need no lane shifts.
 
-template <typename S>
-struct TubeEdges {
-    S v[2][kWaves][2][4][12];      // [slot][wave][lane 0 / 63][row][x-moving population]
+// One buffer (a second barrier per level) for FP64 blocks of several waves
+// per row, so that 64 KB of LDS hold a block and sixteen waves fit a CU (the
+// 512-tube batch: 59.2 us per step against 93.6 with two buffers); two where
+// few blocks run, each a chain of levels (400 x 4 tube: 1.46 against 1.55 us).
+template <typename S, int NY, int WC>
+struct TubeRows {
+    static constexpr int kBuffers = sizeof(S) == 8 && WC > 1 ? 1 : 2;
+    // [buffer][row][one element before and after the 16 sub-rows]
+    S v[kBuffers][NY][16 * 64 * WC + 2];
 };
 
-template <typename S, typename C, bool COMP, bool NT, int L, int NY>
-__device__ __forceinline__ void tube_block(ConstInst* __restrict__ P, int x0,
+template <typename S, typename C, bool COMP, bool NT, int NY, int WC>
+__device__ __forceinline__ void tube_block(ConstInst* __restrict__ P, int x0, int overlap, int steps,
                                            const S* __restrict__ fin, S* __restrict__ fout,
-                                           unsigned* __restrict__ health, TubeEdges<S>& lds) {
-    static_assert(L % 2 == 0, "levels alternate between two register sets");
+                                           unsigned* __restrict__ health, TubeRows<S, NY, WC>& lds) {
     static_assert(NY == 1 || NY == 2 || NY == 4, "one, two or four rows");
+    constexpr int CW = 64 * WC;
     const int lane = lane_id();
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l = 64 * wv + lane;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = wid / WC, cw = wid % WC;
+    const int l = 64 * cw + lane;
     const int nx = P->nx;
-    const int x = x0 - L + l;
-    const long long plane = P->plane;
-    const S* __restrict__ fi = fin + P->off;
-    S* __restrict__ fo = fout + P->off;
-    const unsigned origin = unsigned(P->origin), pitch = unsigned(P->pitch);
-    // load column: lanes outside the grid and its ghost ring read the ghost
-    // column of their side (values that reach no stored cell)
-    const unsigned cx = unsigned(x < -1 ? -1 : (x > nx ? nx : x));
+    const int x = x0 - overlap + l;
+    const unsigned long long pstep = (unsigned long long)P->plane * sizeof(S);
+    const unsigned ro = unsigned(P->origin) + unsigned(row) * unsigned(P->pitch);
+    // row pointers at column -1, as in step2_block; lanes outside the grid and
+    // its ghost ring load the ghost column of their side
+    auto row_at = [&](unsigned long long base) {
+        return base + ((unsigned long long)ro - 1u) * sizeof(S);
+    };
+    const unsigned bcx = unsigned((x < -1 ? -1 : (x > nx ? nx : x)) + 1) * unsigned(sizeof(S));
     const C b = C(P->b), binv = C(P->binv);
     // whether this wave holds the west (x = -1) or east (x = nx) ghost column
-    const int xw = x0 - L + 64 * wv;
+    const int xw = x0 - overlap + 64 * cw;
     const bool wave_west = xw <= -1 && xw + 63 >= -1, wave_east = xw <= nx && xw + 63 >= nx;
-    const bool edge_lane = lane == 0 || lane == 63;
-    const int eside = lane == 0 ? 0 : 1;
-    const int nwave = lane == 0 ? wv - 1 : wv + 1;
-    const int nside = lane == 0 ? 1 : 0;
-    const bool hlds = edge_lane && nwave >= 0 && nwave < kWaves;
     bool healthy = true;
 
-    S A[NY][16], B[NY][16];
-#pragma unroll
-    for (int r = 0; r < NY; ++r) {
-        const unsigned o = origin + unsigned(r) * pitch;
+    S f[16];
+    {
+        unsigned long long a = row_at(reinterpret_cast<unsigned long long>(fin + P->off));
+        const unsigned bo = lane_off(bcx);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            A[r][i] = (fi + (long long)i * plane)[o + cx];
-            B[r][i] = S(0);
+            f[i] = gload<S>(a, bo);
+            if (i < 15) a = next_pop(a, pstep);
         }
     }
-    // dst = level k + 1 from src = level k
-    auto level = [&](S (&src)[NY][16], S (&dst)[NY][16], int k) {
+    for (int k = 0; k < steps; ++k) {
         // the ghost columns: their side's equilibrium at every level (the
         // side index is wave-uniform, so the values come from scalar loads)
         if (k > 0 && wave_west && x == -1) {
 #pragma unroll
-            for (int r = 0; r < NY; ++r)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) src[r][i] = S(P->ghost[XLO][i]);
+            for (int i = 0; i < 16; ++i) f[i] = S(P->ghost[XLO][i]);
         }
         if (k > 0 && wave_east && x == nx) {
 #pragma unroll
-            for (int r = 0; r < NY; ++r)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) src[r][i] = S(P->ghost[XHI][i]);
+            for (int i = 0; i < 16; ++i) f[i] = S(P->ghost[XHI][i]);
         }
-        if (edge_lane) {
+        constexpr int kBuffers = TubeRows<S, NY, WC>::kBuffers;
+        const int buf = kBuffers == 2 ? k & 1 : 0;
+        S* own = &lds.v[buf][row][1 + l];
+        const S* south = &lds.v[buf][(row + NY - 1) % NY][1 + l];
+        const S* north = &lds.v[buf][(row + 1) % NY][1 + l];
 #pragma unroll
-            for (int r = 0; r < NY; ++r)
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (moves_x(i)) lds.v[k & 1][wv][eside][r][xslot(i)] = src[r][i];
-        }
+        for (int i = 0; i < 16; ++i)
+            if (NY > 1 || moves_x(i)) own[i * CW] = f[i];
         __syncthreads();
-        const bool valid = l > k && l < 255 - k && x >= 0 && x < nx;
         ConstInst* __restrict__ Pc = reload(P);
+        S cdt[16];
+        C rho, Pp;
+        cell_collision<C, COMP>(f, b, binv, Pc->sdt, cdt, rho, Pp);
+        const bool valid = l > k && l < CW - 1 - k && x >= 0 && x < nx;
+        healthy = healthy && (!valid || (rho > C(0) && Pp > C(0)));
 #pragma unroll
-        for (int r = 0; r < NY; ++r) {
-            S h[16];
-            no_value(h);
-            if (hlds) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (moves_x(i)) h[i] = lds.v[k & 1][nwave][nside][r][xslot(i)];
-            }
-            S cdt[16];
-            C rho, Pp;
-            cell_collision<C, COMP>(src[r], b, binv, Pc->sdt, cdt, rho, Pp);
-            healthy = healthy && (!valid || (rho > C(0) && Pp > C(0)));
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const S W = moves_x(i) ? from_left(src[r][i], h[i]) : S(0);
-                const S E = moves_x(i) ? from_right(src[r][i], h[i]) : S(0);
-                dst[r][i] = site_update(Pc, i, src[r][i], W, E, src[(r + NY - 1) % NY][i],
-                                        src[(r + 1) % NY][i], cdt[i]);
-            }
-            // the row's new values are materialised here, in row order: left
-            // free, the compiler sinks every row's update to the next level
-            // and overlaps the four rows' collisions (412 registers)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(dst[r][i]));
+        for (int i = 0; i < 16; ++i) {
+            const S W = moves_x(i) ? own[i * CW - 1] : S(0), E = moves_x(i) ? own[i * CW + 1] : S(0);
+            const S So = moves_y(i) && NY > 1 ? south[i * CW] : f[i];
+            const S N = moves_y(i) && NY > 1 ? (NY == 2 ? So : north[i * CW]) : f[i];
+            f[i] = site_update(Pc, i, f[i], W, E, So, N, cdt[i]);
         }
-    };
-    for (int k = 0; k < L; k += 2) {
-        level(A, B, k);
-        level(B, A, k + 1);
+        if constexpr (kBuffers == 1) __syncthreads();
     }
-    if (x >= 0 && x < nx && l >= L && l <= 255 - L) {
+    if (x >= 0 && x < nx && l >= overlap && l < CW - overlap) {
+        unsigned long long a = row_at(reinterpret_cast<unsigned long long>(fout + P->off));
+        const unsigned bo = lane_off(bcx);
 #pragma unroll
-        for (int r = 0; r < NY; ++r) {
-            const unsigned o = origin + unsigned(r) * pitch + unsigned(x);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                S* p = fo + (long long)i * plane + o;
-                if constexpr (NT)
-                    __builtin_nontemporal_store(A[r][i], p);
-                else
-                    *p = A[r][i];
-            }
+        for (int i = 0; i < 16; ++i) {
+            gstore<S, NT>(a, bo, f[i]);
+            if (i < 15) a = next_pop(a, pstep);
         }
     }
     if (!healthy) atomicOr(health, 1u);
 }
 
-// Two blocks (two waves per SIMD) per CU; FP64 storage with four rows holds
-// two register sets of 64 doubles per lane: one.
-template <typename S, int NY>
-constexpr int tube_waves() { return sizeof(S) == 8 && NY == 4 ? 1 : 2; }
-
-template <typename S, typename C, bool COMP, bool NT, int L, int NY>
-__global__ __launch_bounds__(256, (tube_waves<S, NY>())) void tube_kernel(
-        const Inst* __restrict__ insts, const Item* __restrict__ items, int nitems,
+// Four waves per SIMD: 68-97 VGPRs in FP32 storage, 111-121 in FP64.
+template <typename S, typename C, bool COMP, bool NT, int NY, int WC>
+__global__ __launch_bounds__(64 * NY * WC, 4) void tube_kernel(
+        const Inst* __restrict__ insts, const Item* __restrict__ items, int nitems, int overlap, int steps,
         const S* __restrict__ fin, S* __restrict__ fout, unsigned* __restrict__ health) {
-    __shared__ TubeEdges<S> lds;
+    __shared__ TubeRows<S, NY, WC> lds;
     ConstInst* cinsts = (ConstInst*)insts;
     ConstItem* citems = (ConstItem*)items;
     // XCD-aware item order as in step_kernel
     const int per = (nitems + 7) >> 3;
-    for (int q = blockIdx.x; q < 8 * per; q += gridDim.x) {
-        const int w = (q & 7) * per + (q >> 3);
-        if (w >= nitems) continue;
-        tube_block<S, C, COMP, NT, L, NY>(cinsts + citems[w].inst, citems[w].x0, fin, fout, health, lds);
-        __syncthreads();   // the next item reuses the LDS buffers
-    }
+    const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (w >= nitems) return;
+    tube_block<S, C, COMP, NT, NY, WC>(cinsts + citems[w].inst, citems[w].x0, overlap, steps, fin, fout,
+                                       health, lds);
 }
 
 // --------------------------------------------------------- level pipeline
@@ -1974,37 +1947,37 @@ hipError_t launch_step2(const Inst* insts, const Item* items, int nitems, const 
     return hipGetLastError();
 }
 
-template <typename S, typename C, bool COMP, bool NT>
-void launch_tube_nt(const Inst* insts, const Item* items, int nitems, const S* fin, S* fout,
-                    unsigned* health, int blocks, int ny, hipStream_t st) {
-    switch (ny) {
-        case 1:
-            hipLaunchKernelGGL((tube_kernel<S, C, COMP, NT, kTubeSteps, 1>), dim3(blocks), dim3(256), 0,
-                               st, insts, items, nitems, fin, fout, health);
-            break;
-        case 2:
-            hipLaunchKernelGGL((tube_kernel<S, C, COMP, NT, kTubeSteps, 2>), dim3(blocks), dim3(256), 0,
-                               st, insts, items, nitems, fin, fout, health);
-            break;
-        default:
-            hipLaunchKernelGGL((tube_kernel<S, C, COMP, NT, kTubeSteps, 4>), dim3(blocks), dim3(256), 0,
-                               st, insts, items, nitems, fin, fout, health);
-            break;
-    }
+template <typename S, typename C, bool COMP, int NY, int WC>
+void launch_tube_shape(const Inst* insts, const Item* items, int nitems, int overlap, int steps,
+                       const S* fin, S* fout, unsigned* health, bool nt, hipStream_t st) {
+    const dim3 blocks(8 * ((nitems + 7) / 8)), threads(64 * NY * WC);
+    if (nt)
+        hipLaunchKernelGGL((tube_kernel<S, C, COMP, true, NY, WC>), blocks, threads, 0, st, insts, items,
+                           nitems, overlap, steps, fin, fout, health);
+    else
+        hipLaunchKernelGGL((tube_kernel<S, C, COMP, false, NY, WC>), blocks, threads, 0, st, insts, items,
+                           nitems, overlap, steps, fin, fout, health);
 }
 
 template <typename S, typename C, bool COMP>
-hipError_t launch_tube(const Inst* insts, const Item* items, int nitems, const void* fin, void* fout,
-                       unsigned* health, int grid, bool nt, int ny, hipStream_t st) {
+hipError_t launch_tube(const Inst* insts, const Item* items, int nitems, int waves, int overlap, int steps,
+                       const void* fin, void* fout, unsigned* health, bool nt, int ny, hipStream_t st) {
     if (nitems <= 0) return hipSuccess;
-    if (ny != 1 && ny != 2 && ny != 4) return hipErrorInvalidValue;
-    const int blocks = grid > 0 ? grid : 8 * ((nitems + 7) / 8);
+    if (steps < 1 || steps > overlap || tube_width(waves, overlap) < 1) return hipErrorInvalidValue;
     const S* in = static_cast<const S*>(fin);
     S* out = static_cast<S*>(fout);
-    if (nt)
-        launch_tube_nt<S, C, COMP, true>(insts, items, nitems, in, out, health, blocks, ny, st);
-    else
-        launch_tube_nt<S, C, COMP, false>(insts, items, nitems, in, out, health, blocks, ny, st);
+#define MRT_TUBE(NY, WC) \
+    case 8 * NY + WC: launch_tube_shape<S, C, COMP, NY, WC>(insts, items, nitems, overlap, steps, in, out, health, nt, st); break
+    switch (8 * ny + waves) {
+        MRT_TUBE(1, 1);
+        MRT_TUBE(1, 4);
+        MRT_TUBE(2, 1);
+        MRT_TUBE(2, 2);
+        MRT_TUBE(4, 1);
+        MRT_TUBE(4, 2);
+        default: return hipErrorInvalidValue;
+    }
+#undef MRT_TUBE
     return hipGetLastError();
 }
 
@@ -2057,14 +2030,15 @@ hipError_t k_step2(int prec, const Inst* insts, const Item* items, int nitems, c
     }
 }
 
-// kTubeSteps steps of tubes of ny = 1, 2 or 4 periodic rows (every
-// instance of the launch) with fixed-equilibrium x sides, from fin to fout.
-hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, const void* fin,
-                  void* fout, unsigned* health, int grid, bool nt, int ny, hipStream_t st) {
+// `steps` <= overlap steps of tubes of ny = 1, 2 or 4 periodic rows (every
+// instance of the launch) with fixed-equilibrium x sides, from fin to fout;
+// the items are tube_width(waves, overlap) columns wide.
+hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, int waves, int overlap,
+                  int steps, const void* fin, void* fout, unsigned* health, bool nt, int ny, hipStream_t st) {
     switch (prec) {
-        case 0: return launch_tube<double, double, false>(insts, items, nitems, fin, fout, health, grid, nt, ny, st);
-        case 1: return launch_tube<float, float, true>(insts, items, nitems, fin, fout, health, grid, nt, ny, st);
-        case 2: return launch_tube<float, double, false>(insts, items, nitems, fin, fout, health, grid, nt, ny, st);
+        case 0: return launch_tube<double, double, false>(insts, items, nitems, waves, overlap, steps, fin, fout, health, nt, ny, st);
+        case 1: return launch_tube<float, float, true>(insts, items, nitems, waves, overlap, steps, fin, fout, health, nt, ny, st);
+        case 2: return launch_tube<float, double, false>(insts, items, nitems, waves, overlap, steps, fin, fout, health, nt, ny, st);
         default: return hipErrorInvalidValue;
     }
 }

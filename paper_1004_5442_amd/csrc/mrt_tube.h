@@ -4,9 +4,13 @@
 
 namespace mrt {
 
-// Time steps per pass, and the columns one block stores: its 256 lanes less
-// the recomputed overlap of one column per step on either side.
+// The number of time steps per pass by which the library names the tube
+// march (the least it takes; a launch takes up to kTubeMaxSteps).
 constexpr int kTubeSteps = 4;
-constexpr int kTubeWidth = 256 - 2 * kTubeSteps;
+constexpr int kTubeMaxSteps = 24;
+
+// Columns a block of `waves` 64-column waves stores after `steps` steps: its
+// lanes less the recomputed overlap of one column per step on either side.
+constexpr int tube_width(int waves, int steps) { return 64 * waves - 2 * steps; }
 
 }  // namespace mrt

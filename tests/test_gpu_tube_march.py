@@ -290,3 +290,30 @@ def test_tube_march_prepared_graphs_and_autotuned_single_grid():
     assert d <= tol
     tuned.close()
     one.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_eq64", "fp32"])
+@pytest.mark.parametrize("ny", [1, 2, 4])
+def test_large_batches_take_wide_blocks(ny, precision):
+    """Batches large enough for blocks of several waves per row (128 or 256
+    columns, eight steps per launch): 21 steps (two launches and one of five
+    steps) against single steps, on tubes that end at the blocks' edges
+    (112 or 240 stored columns) and between them.  The FP32 storage forms
+    round every level alike (bit-identical; two FP32 ulps with FP64
+    collision), FP64 to rounding order."""
+    cases = []
+    for nx in (1, 111, 112, 113, 239, 240, 241, 480, 3989):
+        cases += W.tube_batch(1, seed=nx, nx_range=(nx, nx), ny=ny)
+    cases += W.tube_batch(400 // ny, seed=3, nx_range=(1500, 2500), ny=ny)
+    one = Batch(cases, precision)
+    one.set_steps_per_pass(1)
+    tube = Batch(cases, precision)
+    print(f"wide tube blocks ny={ny} {precision}", flush=True)
+    one.step(21)
+    tube.step(21)
+    for i in [*range(9), 9, len(cases) // 2, len(cases) - 1]:
+        a, b = tube.populations(i), one.populations(i)
+        d = float(np.max(np.abs(a - b)) / np.abs(b).max())
+        assert d <= {"fp64": 1e-13, "fp32_eq64": 2.4e-7, "fp32": 0.0}[precision], (i, d)
+    one.close()
+    tube.close()
