@@ -1797,12 +1797,16 @@ __global__ __launch_bounds__(256) void init_kernel(const Inst* __restrict__ P, c
     }
 }
 
-// Macroscopic fields (FP64) and health of each cell.
+// Macroscopic fields (FP64) and health of each cell.  seen (may be NULL): a
+// word in host memory that is set if the health flag was set when the kernel
+// began or a cell sets it now.
 template <typename S>
 __global__ __launch_bounds__(256) void moments_kernel(const Inst* __restrict__ P,
                                                       const S* __restrict__ f, double* rho,
                                                       double* ux, double* uy, double* T,
-                                                      unsigned* __restrict__ health) {
+                                                      unsigned* __restrict__ health,
+                                                      volatile unsigned* seen) {
+    if (seen && blockIdx.x == 0 && threadIdx.x == 0 && *health) *seen = 1u;
     const long long n = (long long)P->nx * P->ny;
     for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < n;
          c += (long long)gridDim.x * blockDim.x) {
@@ -1817,7 +1821,10 @@ __global__ __launch_bounds__(256) void moments_kernel(const Inst* __restrict__ P
         if (ux) ux[c] = u;
         if (uy) uy[c] = v;
         if (T) T[c] = t;
-        if (!(r > 0.0 && t > 0.0)) atomicOr(health, 1u);
+        if (!(r > 0.0 && t > 0.0)) {
+            atomicOr(health, 1u);
+            if (seen) *seen = 1u;
+        }
     }
 }
 
@@ -2173,12 +2180,13 @@ hipError_t k_init(int prec, const Inst* P, long long cells, const double* rho, c
 }
 
 hipError_t k_moments(int prec, const Inst* P, long long cells, const void* f, double* rho,
-                     double* ux, double* uy, double* T, unsigned* health, hipStream_t st) {
+                     double* ux, double* uy, double* T, unsigned* health, hipStream_t st,
+                     volatile unsigned* seen) {
     const int g = grid_for(cells);
     if (prec == 0)
-        hipLaunchKernelGGL((moments_kernel<double>), dim3(g), dim3(256), 0, st, P, static_cast<const double*>(f), rho, ux, uy, T, health);
+        hipLaunchKernelGGL((moments_kernel<double>), dim3(g), dim3(256), 0, st, P, static_cast<const double*>(f), rho, ux, uy, T, health, seen);
     else
-        hipLaunchKernelGGL((moments_kernel<float>), dim3(g), dim3(256), 0, st, P, static_cast<const float*>(f), rho, ux, uy, T, health);
+        hipLaunchKernelGGL((moments_kernel<float>), dim3(g), dim3(256), 0, st, P, static_cast<const float*>(f), rho, ux, uy, T, health, seen);
     return hipGetLastError();
 }
 
