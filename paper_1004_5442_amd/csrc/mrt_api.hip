@@ -19,6 +19,7 @@
 #include "mrt_dual.h"
 #include "mrt_internal.h"
 #include "mrt_pipe.h"
+#include "mrt_tile.h"
 #include "mrt_tube.h"
 #include "../../include/mrtlb.h"
 
@@ -31,6 +32,8 @@ hipError_t k_step2(int prec, const Inst* insts, const Item* items, int nitems, c
                    void* fout, unsigned* health, int grid, bool nt, bool wrap4, hipStream_t st);
 hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, int waves, int overlap,
                   int steps, const void* fin, void* fout, unsigned* health, bool nt, int ny, hipStream_t st);
+hipError_t k_tile(int prec, const Inst* insts, const Item* items, int nitems, int rows, int overlap,
+                  int steps, bool walls, const void* fin, void* fout, unsigned* health, hipStream_t st);
 hipError_t k_pipe(int prec, int waves, const Inst* insts, const Item* items, int nitems, const void* fin,
                   void* fout, unsigned* health, bool nt, hipStream_t st);
 hipError_t k_variant(int prec, const Inst* P, int nx, int ny, int scheme, bool reflect,
@@ -392,22 +395,53 @@ PipeShape pipe_shape(int nx, int ny, int prec, int rows) {
     return best;
 }
 
-// Whether a grid runs the level pipeline by default: where its launch, cost
-// row iterations for four steps, is expected to be shorter than four steps of
-// the form it would run otherwise (per_pass 1 or 2).  Microseconds of one
-// iteration and site updates per microsecond of the other forms as measured
-// (FP64, FP32, FP32 with FP64 collision); the one-step kernel adds its launch.
-// Measured per step, other form -> pipeline: FP64 360 x 100 5.6 -> 5.9
-// (stays), 400 x 300 11.4 -> 7.8, 512^2 15.4 -> 10.8, 1024^2 39.3 -> 22.9,
-// 4096^2 575 -> 282; FP32 with FP64 collision 512^2 9.4 -> 10.2 (stays), 700^2
-// 16.2 -> 12.4, 1024^2 22.2 -> 19.3, 4096^2 279 -> 198; FP32 512^2 9.9 -> 10.1
-// (stays), 700^2 17.2 -> 12.1, 4096^2 312 -> 205.
-bool pipe_default(int nx, int ny, int prec, int per_pass, const PipeShape& shape) {
+// Launch shape of the tile march: rows per block and steps per launch (the
+// overlap recomputed on every side), and its expected microseconds per step: a
+// launch's start, and per step the longer of one wave's chain of dependent
+// instructions and the resident waves' throughput.  A reflecting side lengthens
+// the chain of the blocks at it.  Measured per step, FP32 with FP64 collision:
+// 256^2 periodic 12 rows x 3 steps 3.5 us, 16 x 4 3.7, 8 x 2 4.6, 12 x 4 (more
+// blocks than CUs) 5.6, the one-step kernel 4.6; 360 x 100 with a wall 8 x 2 4.5,
+// 12 x 4 4.6, 12 x 3 5.0, one step 5.3.
+struct TileShape {
+    int rows = 8, steps = 1;
+    double us = -1;
+};
+TileShape tile_shape(int nx, int ny, int prec, const int bc[4]) {
+    const bool fp64 = prec == MRT_FP64, walls = has_kind(bc, MRT_BC_REFLECT);
+    const double start = 4.0, chain = 1.4, wave = fp64 ? 1.05 : 0.69, wall = walls ? 0.9 : 0.0;
+    const int most = !fp64 ? 16 : walls ? 8 : 12;
+    TileShape best;
+    for (int rows = 8; rows <= most; rows += 4)
+        for (int steps = 2; steps <= mrt::kTileMaxSteps && 2 * steps < rows; ++steps) {
+            const int w = mrt::tile_width(steps), h = mrt::tile_height(rows, steps);
+            const double blocks = double((nx + w - 1) / w) * ((ny + h - 1) / h);
+            const double level = std::max(chain, std::ceil(blocks / 256.0) * rows / 4.0 * wave) + wall;
+            const double us = (start + steps * level) / steps;
+            if (best.us < 0 || us < best.us) best = TileShape{rows, steps, us};
+        }
+    return best;
+}
+
+// The form a grid runs by default, beside the tube march: the one expected to
+// take the fewest microseconds per step of the form it would run otherwise
+// (per_pass 1 or 2), the level pipeline (cost row iterations for four steps)
+// and the tile march.  Microseconds of one iteration and site updates per
+// microsecond as measured (FP64, FP32, FP32 with FP64 collision); the one-step
+// kernel adds its launch.  Measured per step, other form -> pipeline: FP64
+// 360 x 100 5.6 -> 5.9 (stays), 400 x 300 11.4 -> 7.8, 512^2 15.4 -> 10.8,
+// 1024^2 39.3 -> 22.9, 4096^2 575 -> 282; FP32 with FP64 collision 512^2 9.4 ->
+// 10.2 (stays), 700^2 16.2 -> 12.4, 1024^2 22.2 -> 19.3, 4096^2 279 -> 198;
+// FP32 512^2 9.9 -> 10.1 (stays), 700^2 17.2 -> 12.1, 4096^2 312 -> 205.
+enum class Form { Steps, Pipe, Tile };
+Form default_form(int nx, int ny, int prec, int per_pass, const PipeShape& pipe, const TileShape& tile) {
     const double iteration[3] = {2.0, 2.4, 2.45};
     const double rate1[3] = {18500, 33000, 35000}, rate2[3] = {28000, 53000, 54000};
     const double cells = (double)nx * ny;
-    const double other = per_pass == 2 ? cells / rate2[prec] : 2.2 + cells / rate1[prec];
-    return shape.cost * iteration[prec] / kPipeSteps < other;
+    const double steps = per_pass == 2 ? cells / rate2[prec] : std::max(4.3, 2.2 + cells / rate1[prec]);
+    const double piped = pipe.cost * iteration[prec] / kPipeSteps;
+    if (tile.us < steps && tile.us < piped) return Form::Tile;
+    return piped < steps ? Form::Pipe : Form::Steps;
 }
 
 // Launch shape of the tube march: waves per row (a block holds 64 x waves
@@ -496,7 +530,12 @@ struct mrt_ctx {
     Item* d_items_p = nullptr;       // its work items
     int nitems_p = 0, rows_p = 0, waves_p = 2;
     GraphCache graphs_p;             // captured pipeline passes
-    bool ghosts_stale = false;       // reflecting-wall ghosts of the current state (the pipeline writes none)
+    bool tile = false;               // several steps at a time by the tile march
+    TileShape tile_form;
+    Item* d_items_t = nullptr;       // its work items
+    int nitems_t = 0;
+    GraphCache graphs_t;             // captured tile-march passes
+    bool ghosts_stale = false;       // reflecting-wall ghosts of the current state (the pipeline and the tile march write none)
     bool eager = false;              // launch step by step (the tile autotuner)
     int scheme = 0;                  // MRT_SCHEME_* flags
     void* f_tmp = nullptr;           // post-collision state of the split scheme
@@ -619,6 +658,22 @@ int build_items_pipe(mrt_ctx* c, const PipeShape& shape) {
     return MRT_OK;
 }
 
+int build_items_tile(mrt_ctx* c, const TileShape& shape) {
+    std::string& ctx_err = c->err;
+    const int w = mrt::tile_width(shape.steps), h = mrt::tile_height(shape.rows, shape.steps);
+    std::vector<Item> items;
+    for (int y = 0; y < c->ny; y += h)
+        for (int x = 0; x < c->nx; x += w) items.push_back(Item{0, x, y, std::min(c->ny, y + h)});
+    if (c->d_items_t) HIPTRY(hipFree(c->d_items_t));
+    c->d_items_t = nullptr;
+    HIPTRY(hipMalloc(&c->d_items_t, items.size() * sizeof(Item)));
+    HIPTRY(hipMemcpy(c->d_items_t, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
+    c->nitems_t = int(items.size());
+    c->tile_form = shape;
+    c->graphs_t.clear();
+    return MRT_OK;
+}
+
 // Work items of the adjoint kernel: 256-column chunks of row bands, marched
 // like the one-step kernel's.  Bands of up to 16 rows while the grid still
 // gives ~2048 items (four blocks per block slot of the chip at two 4-wave
@@ -652,6 +707,9 @@ constexpr long long kNonTemporalBytes = 256LL << 20;
 // the launch latency dominates there); larger ones refill them with the
 // ghost kernel, which costs them less than the extra registers would.
 constexpr long long kWallsInKernelCells = 1LL << 22;
+
+// The autotuner times the tile march on grids of up to this many cells.
+constexpr long long kTileCells = 1LL << 20;
 
 int check_health(mrt_ctx* c) {
     std::string& ctx_err = c->err;
@@ -743,10 +801,15 @@ int mrt_init_grid(mrt_ctx** out, int nx, int ny, int precision, const int bc[4],
         if (build_items4(c) != MRT_OK) return fail(MRT_EDEVICE);
         c->per_pass = kTubeSteps;
     } else {
-        const PipeShape shape = pipe_shape(nx, ny, precision, 0);
-        if (pipe_default(nx, ny, precision, c->per_pass, shape)) {
-            if (build_items_pipe(c, shape) != MRT_OK) return fail(MRT_EDEVICE);
+        const PipeShape pipe = pipe_shape(nx, ny, precision, 0);
+        const TileShape tile = tile_shape(nx, ny, precision, bc);
+        const Form form = default_form(nx, ny, precision, c->per_pass, pipe, tile);
+        if (form == Form::Pipe) {
+            if (build_items_pipe(c, pipe) != MRT_OK) return fail(MRT_EDEVICE);
             c->pipe = true;
+        } else if (form == Form::Tile) {
+            if (build_items_tile(c, tile) != MRT_OK) return fail(MRT_EDEVICE);
+            c->tile = true;
         }
     }
     (void)ctx_err;
@@ -845,6 +908,32 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
         if (launch) c->ghosts_stale = reflect;
         n -= passes * kPipeSteps;
         if (n == 0) return MRT_OK;
+    }
+    if (c->tile && c->scheme == 0) {
+        // the tile march: passes of tile_form.steps steps, then one of the
+        // remaining steps.  Every step runs the same code however the passes
+        // are cut, so that n steps at once and one at a time agree bit for bit
+        auto march = [&](int cur, hipStream_t st, int steps) -> hipError_t {
+            return mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
+                               c->tile_form.steps, steps, reflect, c->f[cur], c->f[1 - cur], c->d_health, st);
+        };
+        auto enqueue_t = [&](int cur, hipStream_t st) -> hipError_t { return march(cur, st, c->tile_form.steps); };
+        const int passes = n / c->tile_form.steps, rest = n % c->tile_form.steps;
+        if (c->eager || passes == 1) {
+            if (launch)
+                for (int k = 0; k < passes; ++k) {
+                    HIPTRY(enqueue_t(c->cur, c->stream));
+                    c->cur ^= 1;
+                }
+        } else if (passes > 1) {
+            HIPTRY(run_graphs(c->graphs_t, c->cur, passes, c->stream, enqueue_t, launch));
+        }
+        if (launch && rest) {
+            HIPTRY(march(c->cur, c->stream, rest));
+            c->cur ^= 1;
+        }
+        if (launch && n) c->ghosts_stale = reflect;
+        return MRT_OK;
     }
     // the one-step kernel that keeps the wall ghosts itself expects them
     // current; the other forms refill them
@@ -1059,7 +1148,7 @@ int mrt_set_steps_per_pass(mrt_ctx* c, int steps, int rows) {
         }
     }
     c->per_pass = steps;
-    c->pipe = false;
+    c->pipe = c->tile = false;
     c->graphs.clear();
     c->graphs2.clear();
     c->graphs4.clear();
@@ -1084,6 +1173,7 @@ int mrt_set_pipeline(mrt_ctx* c, int rows) {
         }
     }
     c->pipe = rows >= 0;
+    c->tile = false;
     return MRT_OK;
 }
 
@@ -1153,7 +1243,7 @@ int mrt_autotune(mrt_ctx* c, int steps) {
     const int row_opts[] = {1, 2, 3, 4, 5, 6, 8, 12, 16, 32, 64, 128};
     const int grid_mult[] = {0, 2, 4, 8};
     c->per_pass = 1;
-    c->pipe = false;
+    c->pipe = c->tile = false;
     float best = 1e30f;
     int best_rows = c->rows, best_grid = c->grid;
     for (int r : row_opts) {
@@ -1232,6 +1322,28 @@ int mrt_autotune(mrt_ctx* c, int steps) {
         c->ghosts_stale = false;     // the saved state has them
         HIPTRY(hipMemcpyAsync(c->f[c->cur], save, bytes, hipMemcpyDeviceToDevice, c->stream));
     }
+    // the tile march, per step
+    bool best_tile = false;
+    if (c->scheme == 0 && (long long)c->nx * c->ny <= kTileCells) {
+        if (build_items_tile(c, tile_shape(c->nx, c->ny, c->prec, c->bc)) != MRT_OK) return MRT_EDEVICE;
+        const int t = c->tile_form.steps, stepst = t * std::max(1, (steps + t - 1) / t);
+        c->tile = c->eager = true;
+        mrt_step(c, t);
+        HIPTRY(hipEventRecord(e0, c->stream));
+        mrt_step(c, stepst);
+        HIPTRY(hipEventRecord(e1, c->stream));
+        c->tile = c->eager = false;
+        HIPTRY(hipEventSynchronize(e1));
+        float ms = 0;
+        HIPTRY(hipEventElapsedTime(&ms, e0, e1));
+        if (ms / float(stepst) < best) {
+            best = ms / float(stepst);
+            best_tile = true;
+            best_pipe = false;
+        }
+        c->ghosts_stale = false;     // the saved state has them
+        HIPTRY(hipMemcpyAsync(c->f[c->cur], save, bytes, hipMemcpyDeviceToDevice, c->stream));
+    }
     // the tube march, per step
     if (tube_inst_ok(c->inst) && c->scheme == 0) {
         if (build_items4(c) != MRT_OK) return MRT_EDEVICE;
@@ -1249,7 +1361,7 @@ int mrt_autotune(mrt_ctx* c, int steps) {
         if (ms / float(steps4) < best) {
             best = ms / float(steps4);
             best_pass = kTubeSteps;
-            best_pipe = false;
+            best_pipe = best_tile = false;
         }
         HIPTRY(hipMemcpyAsync(c->f[c->cur], save, bytes, hipMemcpyDeviceToDevice, c->stream));
     }
@@ -1259,6 +1371,7 @@ int mrt_autotune(mrt_ctx* c, int steps) {
     HIPTRY(hipFree(save));
     HIPTRY(hipMemsetAsync(c->d_health, 0, sizeof(unsigned), c->stream));
     c->pipe = best_pipe;
+    c->tile = best_tile;
     if (build_items(c, best_rows) != MRT_OK) return MRT_EDEVICE;
     c->grid = best_grid;
     c->per_pass = best_pass;
@@ -1283,11 +1396,13 @@ void mrt_destroy(mrt_ctx* c) {
     if (c->d_items2) (void)hipFree(c->d_items2);
     if (c->d_items4) (void)hipFree(c->d_items4);
     if (c->d_items_p) (void)hipFree(c->d_items_p);
+    if (c->d_items_t) (void)hipFree(c->d_items_t);
     if (c->f_tmp) (void)hipFree(c->f_tmp);
     c->graphs.clear();
     c->graphs2.clear();
     c->graphs4.clear();
     c->graphs_p.clear();
+    c->graphs_t.clear();
     if (c->d_stage) (void)hipFree(c->d_stage);
     if (c->d_partial) (void)hipFree(c->d_partial);
     if (c->d_health) (void)hipFree(c->d_health);

@@ -1684,6 +1684,193 @@ __global__ __launch_bounds__(64 * kPipeSteps * WC, (pipe_occupancy<S>())) void p
                                fout, health, lds);
 }
 
+// ------------------------------------------------------------ tile march
+
+}  // namespace mrt
+
+#include "mrt_tile.h"
+
+namespace mrt {
+
+// Several time steps per pass for small grids of any boundary kinds, where a
+// step is little more than its launch.  A block of NR waves holds NR rows of 64
+// columns, one row per wave, one cell per lane, covers the cells x0 - overlap ..
+// x0 - overlap + 63, y0 - overlap .. y0 - overlap + NR - 1, advances them
+// `steps` <= overlap steps as the tube march does (every wave puts its row into
+// LDS, a barrier, the collision, the neighbours from LDS) and stores the
+// (64 - 2 overlap) x (NR - 2 overlap) cells that are exact; the rest is
+// recomputed by the neighbouring blocks, on CUs that would otherwise idle.
+//
+// Boundaries: cells outside a periodic side are the wrapped ones.  The ghost
+// cell of a fixed-equilibrium or outflow side is held by its lane as a shadow
+// of the wall cell next to it: the lane holds the wall cell's populations,
+// advances them with the wall cell's neighbours, and puts the side's
+// equilibrium, or the cell itself, into LDS.  Beside a reflecting side the wall
+// cell's lane forms the ghost's value after the exchange and puts it where it
+// reads the ghost (it is the only reader; a shadow lane that formed it before
+// the exchange made every level 1.3 us longer).  No ghost ring is read or
+// written.  Cells further out reach no stored cell.
+template <typename S, int NR>
+struct TileRows {
+    static constexpr int kBuffers = sizeof(S) == 8 ? 1 : 2;      // 131 KB at most
+    // [buffer][row][one element before and after the 16 sub-rows]
+    S v[kBuffers][NR][16 * 64 + 2];
+};
+
+// WALLS: the grid has reflecting sides (their code costs registers: FP64 then
+// runs blocks of eight rows only, 202 VGPRs).
+template <typename S, typename C, bool COMP, int NR, bool WALLS>
+__global__ __launch_bounds__(64 * NR, (NR == 16 ? 4 : NR == 8 && WALLS && sizeof(S) == 8 ? 2 : 3)) void tile_kernel(
+        const Inst* __restrict__ insts, const Item* __restrict__ items, int nitems, int overlap, int steps,
+        const S* __restrict__ fin, S* __restrict__ fout, unsigned* __restrict__ health) {
+    __shared__ TileRows<S, NR> lds;
+    ConstItem* citems = (ConstItem*)items;
+    // XCD-aware item order as in step_kernel
+    const int per = (nitems + 7) >> 3;
+    const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (w >= nitems) return;
+    ConstInst* __restrict__ P = (ConstInst*)insts + citems[w].inst;
+    const int x0 = citems[w].x0, y0 = citems[w].y0;
+    const int lane = lane_id();
+    const int row = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nx = P->nx, ny = P->ny;
+    const int x = x0 - overlap + lane, y = y0 - overlap + row;
+    const C b = C(P->b), binv = C(P->binv);
+    // the cell this lane holds, and where its neighbours' values are in LDS
+    const bool per_x = P->bc[XLO] == BC_PERIODIC, per_y = P->bc[YLO] == BC_PERIODIC;
+    int xs = x, ys = y, cn = lane, rn = row;
+    if (per_x) {
+        xs %= nx;
+        if (xs < 0) xs += nx;
+    } else {
+        xs = x < 0 ? 0 : (x >= nx ? nx - 1 : x);
+        cn = x == -1 ? lane + 1 : (x == nx ? lane - 1 : lane);
+    }
+    if (per_y) {
+        ys %= ny;
+        if (ys < 0) ys += ny;
+    } else {
+        ys = y < 0 ? 0 : (y >= ny ? ny - 1 : y);
+        rn = y == -1 ? row + 1 : (y == ny ? row - 1 : row);
+    }
+    rn = rn < 0 ? 0 : (rn > NR - 1 ? NR - 1 : rn);
+    const int rs = rn > 0 ? rn - 1 : 0, rno = rn < NR - 1 ? rn + 1 : NR - 1;
+    const bool ghost_w = !per_x && x == -1, ghost_e = !per_x && x == nx;
+    // fixed equilibria of the ghost cells this wave holds (a side or -1; rows
+    // are wave-uniform), and the reflecting sides that its cells lie at
+    const int xw = x0 - overlap;
+    const bool eq_w = P->bc[XLO] == BC_EQ && xw <= -1;
+    const bool eq_e = P->bc[XHI] == BC_EQ && xw <= nx && xw + 63 >= nx;
+    const int eq_row = y == -1 && P->bc[YLO] == BC_EQ ? int(YLO) : (y == ny && P->bc[YHI] == BC_EQ ? int(YHI) : -1);
+    // (of the cell held: the shadow of a corner cell has its other wall too, and
+    // puts there what the cell's own lane does; ghosts of reflecting sides are
+    // nobody's shadows)
+    const bool shadow = !((x == -1 && P->bc[XLO] == BC_REFLECT) || (x == nx && P->bc[XHI] == BC_REFLECT) ||
+                          (y == -1 && P->bc[YLO] == BC_REFLECT) || (y == ny && P->bc[YHI] == BC_REFLECT)) &&
+                        (per_x || (x >= -1 && x <= nx)) && (per_y || (y >= -1 && y <= ny));
+    const bool wall_w = shadow && P->bc[XLO] == BC_REFLECT && xs == 0 && cn > 0;
+    const bool wall_e = shadow && P->bc[XHI] == BC_REFLECT && xs == nx - 1 && cn < 63;
+    const bool wall_s = shadow && P->bc[YLO] == BC_REFLECT && ys == 0 && rn > 0;
+    const bool wall_n = shadow && P->bc[YHI] == BC_REFLECT && ys == ny - 1 && rn < NR - 1;
+    const bool walls_y = (P->bc[YLO] == BC_REFLECT && ys == 0 && y >= 0) ||
+                         (P->bc[YHI] == BC_REFLECT && ys == ny - 1 && y < ny);
+    const bool walls_x = (P->bc[XLO] == BC_REFLECT && xw <= 0) ||
+                         (P->bc[XHI] == BC_REFLECT && xw + 63 >= nx - 1);
+    const unsigned long long pstep = (unsigned long long)P->plane * sizeof(S);
+    auto row_at = [&](unsigned long long base, int r) {
+        return base + ((unsigned long long)(unsigned(P->origin) + unsigned(r) * unsigned(P->pitch)) - 1u) * sizeof(S);
+    };
+    const unsigned bcx = unsigned(xs + 1) * unsigned(sizeof(S));
+    bool healthy = true;
+
+    S f[16];
+    {
+        unsigned long long a = row_at(reinterpret_cast<unsigned long long>(fin + P->off), ys);
+        const unsigned bo = lane_off(bcx);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            f[i] = gload<S>(a, bo);
+            if (i < 15) a = next_pop(a, pstep);
+        }
+    }
+    constexpr int kBuffers = TileRows<S, NR>::kBuffers;
+    for (int k = 0; k < steps; ++k) {
+        const int buf = kBuffers == 2 ? k & 1 : 0;
+        {
+            S* own = &lds.v[buf][row][1 + lane];
+            S g[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) g[i] = f[i];
+            if (eq_row >= 0) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) g[i] = S(P->ghost[eq_row][i]);
+            }
+            if (eq_w && ghost_w) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) g[i] = S(P->ghost[XLO][i]);
+            }
+            if (eq_e && ghost_e) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) g[i] = S(P->ghost[XHI][i]);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) own[i * 64] = g[i];
+        }
+        __syncthreads();
+        ConstInst* __restrict__ Pc = reload(P);
+        S* mid = &lds.v[buf][rn][1 + cn];
+        S* south = &lds.v[buf][rs][1 + cn];
+        S* north = &lds.v[buf][rno][1 + cn];
+        if (WALLS && walls_x) {
+            S g[16];
+            reflected_eq<C>(f, 0, b, binv, g);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (moves_x(i)) {
+                    if (wall_w) mid[i * 64 - 1] = g[i];
+                    if (wall_e) mid[i * 64 + 1] = g[i];
+                }
+        }
+        if (WALLS && walls_y) {
+            S g[16];
+            reflected_eq<C>(f, 1, b, binv, g);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (moves_y(i)) {
+                    if (wall_s) south[i * 64] = g[i];
+                    if (wall_n) north[i * 64] = g[i];
+                }
+        }
+        S cdt[16];
+        C rho, Pp;
+        cell_collision<C, COMP>(f, b, binv, Pc->sdt, cdt, rho, Pp);
+        // the neighbours are read after the collision: their registers beside
+        // its own would spill in FP64 (other blocks' waves cover the reads)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(cdt[i]) :: "memory");
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const S W = moves_x(i) ? mid[i * 64 - 1] : S(0), E = moves_x(i) ? mid[i * 64 + 1] : S(0);
+            const S So = moves_y(i) ? south[i * 64] : S(0), N = moves_y(i) ? north[i * 64] : S(0);
+            f[i] = site_update(Pc, i, f[i], W, E, So, N, cdt[i]);
+        }
+        const bool valid = lane >= k && lane < 64 - k && row >= k && row < NR - k && x >= 0 && x < nx &&
+                           y >= 0 && y < ny;
+        healthy = healthy && (!valid || (rho > C(0) && Pp > C(0)));
+        if constexpr (kBuffers == 1) __syncthreads();
+    }
+    if (lane >= overlap && lane < 64 - overlap && row >= overlap && row < NR - overlap && x < nx && y < ny) {
+        unsigned long long a = row_at(reinterpret_cast<unsigned long long>(fout + P->off), y);
+        const unsigned bo = lane_off(bcx);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            gstore<S, false>(a, bo, f[i]);
+            if (i < 15) a = next_pop(a, pstep);
+        }
+    }
+    if (!healthy) atomicOr(health, 1u);
+}
+
 // ------------------------------------------------- scheme variants
 //
 // The two other readings of the paper's time/space discretisation, one
@@ -2046,6 +2233,50 @@ hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, in
         case 0: return launch_tube<double, double, false>(insts, items, nitems, waves, overlap, steps, fin, fout, health, nt, ny, st);
         case 1: return launch_tube<float, float, true>(insts, items, nitems, waves, overlap, steps, fin, fout, health, nt, ny, st);
         case 2: return launch_tube<float, double, false>(insts, items, nitems, waves, overlap, steps, fin, fout, health, nt, ny, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// `steps` <= overlap steps from fin to fout by the tile march (`rows` = 8, 12
+// or 16 rows a block; the items are tile_width(overlap) columns of
+// tile_height(rows, overlap) rows); no ghosts are read.  walls: the grid has
+// reflecting sides (FP64: rows = 8 then, and never 16).
+template <typename S, typename C, bool COMP>
+hipError_t launch_tile(const Inst* insts, const Item* items, int nitems, int rows, int overlap, int steps,
+                       bool walls, const void* fin, void* fout, unsigned* health, hipStream_t st) {
+    if (nitems <= 0) return hipSuccess;
+    if (steps < 1 || steps > overlap || tile_height(rows, overlap) < 1) return hipErrorInvalidValue;
+    const dim3 blocks(8 * ((nitems + 7) / 8)), threads(64 * rows);
+    const S* in = static_cast<const S*>(fin);
+    S* out = static_cast<S*>(fout);
+#define MRT_TILE(NR, WALLS) \
+    hipLaunchKernelGGL((tile_kernel<S, C, COMP, NR, WALLS>), blocks, threads, 0, st, insts, items, nitems, overlap, steps, in, out, health)
+    if (walls && rows == 8) {
+        MRT_TILE(8, true);
+    } else if (rows == 8) {
+        MRT_TILE(8, false);
+    } else if (rows == 12 && !walls) {
+        MRT_TILE(12, false);
+    } else {
+        if constexpr (sizeof(S) == 4) {      // FP64: beyond its registers
+            if (rows == 12) MRT_TILE(12, true);
+            else if (rows == 16 && walls) MRT_TILE(16, true);
+            else if (rows == 16) MRT_TILE(16, false);
+            else return hipErrorInvalidValue;
+        } else {
+            return hipErrorInvalidValue;
+        }
+    }
+#undef MRT_TILE
+    return hipGetLastError();
+}
+
+hipError_t k_tile(int prec, const Inst* insts, const Item* items, int nitems, int rows, int overlap,
+                  int steps, bool walls, const void* fin, void* fout, unsigned* health, hipStream_t st) {
+    switch (prec) {
+        case 0: return launch_tile<double, double, false>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, health, st);
+        case 1: return launch_tile<float, float, true>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, health, st);
+        case 2: return launch_tile<float, double, false>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, health, st);
         default: return hipErrorInvalidValue;
     }
 }
