@@ -33,7 +33,8 @@ hipError_t k_step2(int prec, const Inst* insts, const Item* items, int nitems, c
 hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, int waves, int overlap,
                   int steps, const void* fin, void* fout, unsigned* health, bool nt, int ny, hipStream_t st);
 hipError_t k_tile(int prec, const Inst* insts, const Item* items, int nitems, int rows, int overlap,
-                  int steps, bool walls, const void* fin, void* fout, unsigned* health, hipStream_t st);
+                  int steps, bool walls, const void* fin, void* fout, void* const* fouts, unsigned* health,
+                  hipStream_t st);
 hipError_t k_pipe(int prec, int waves, const Inst* insts, const Item* items, int nitems, const void* fin,
                   void* fout, unsigned* health, bool nt, hipStream_t st);
 hipError_t k_variant(int prec, const Inst* P, int nx, int ny, int scheme, bool reflect,
@@ -915,7 +916,8 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
         // are cut, so that n steps at once and one at a time agree bit for bit
         auto march = [&](int cur, hipStream_t st, int steps) -> hipError_t {
             return mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
-                               c->tile_form.steps, steps, reflect, c->f[cur], c->f[1 - cur], c->d_health, st);
+                               c->tile_form.steps, steps, reflect, c->f[cur], c->f[1 - cur], nullptr, c->d_health,
+                               st);
         };
         auto enqueue_t = [&](int cur, hipStream_t st) -> hipError_t { return march(cur, st, c->tile_form.steps); };
         const int passes = n / c->tile_form.steps, rest = n % c->tile_form.steps;
@@ -1480,15 +1482,31 @@ int mrt_step_checkpointed(mrt_ctx* c, void* f, void* f_tmp, int segment, int nst
     // state is written there by its step directly (no copy), the others go
     // to whichever of f / f_tmp the step does not read
     HIPTRY(hipMemcpyAsync(checkpoints[0], f, bytes, hipMemcpyDeviceToDevice, c->stream));
+    if (c->scheme) return ctx_fail(c, MRT_EINVAL, "explicit-buffer steps use the default scheme only");
+    const bool reflect = has_kind(c->bc, MRT_BC_REFLECT), ring = reflect || has_kind(c->bc, MRT_BC_EQ);
     void* a = f;
-    for (int n = 0; n < nsteps; ++n) {
+    for (int n = 0; n < nsteps;) {
+        // several steps at once, up to the next checkpoint, by the form the
+        // grid runs by default; else one
+        const int togo = std::min(segment - n % segment, nsteps - n);
+        const int m = c->tile ? std::min(togo, c->tile_form.steps) : (c->pipe && togo >= kPipeSteps ? kPipeSteps : 1);
+        n += m;
         void* dst;
-        if ((n + 1) % segment == 0 && n + 1 < nsteps)
-            dst = checkpoints[(n + 1) / segment];
+        if (n % segment == 0 && n < nsteps)
+            dst = checkpoints[n / segment];
         else
             dst = a == f ? f_tmp : f;
-        const int rc = mrt_step_buffers(c, a, dst);
-        if (rc != MRT_OK) return rc;
+        if (c->tile) {
+            HIPTRY(mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
+                               c->tile_form.steps, m, reflect, a, dst, nullptr, c->d_health, c->stream));
+        } else if (m == kPipeSteps) {
+            if (ring) HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, 2 * (c->nx + c->ny), a, 3, c->stream));
+            HIPTRY(mrt::k_pipe(c->prec, c->waves_p, c->d_inst, c->d_items_p, c->nitems_p, a, dst, c->d_health,
+                               c->nt, c->stream));
+        } else {
+            const int rc = mrt_step_buffers(c, a, dst);
+            if (rc != MRT_OK) return rc;
+        }
         a = dst;
     }
     if (a != f) HIPTRY(hipMemcpyAsync(f, a, bytes, hipMemcpyDeviceToDevice, c->stream));
@@ -1541,10 +1559,24 @@ int mrt_adjoint_sweep(mrt_ctx* c, const void* const* checkpoints, int segment, i
     auto state = [&](int seg, int j) -> const void* {
         return j == 0 ? checkpoints[seg] : work[set_of(seg) * w + j - 1];
     };
-    // f^{start + 1} .. f^{stop - 1} of segment seg, one step each as
-    // mrt_step_buffers takes it on a periodic grid (no ghost ring to refill)
+    // f^{start + 1} .. f^{stop - 1} of segment seg, as mrt_step_checkpointed
+    // takes them on a periodic grid (no ghost ring to refill)
     auto recompute = [&](int seg, hipStream_t st) -> hipError_t {
         const int start = seg * segment, stop = std::min(nsteps, start + segment);
+        if (c->tile) {
+            // several states per launch
+            for (int j = 1; j < stop - start;) {
+                const int m = std::min(stop - start - j, c->tile_form.steps);
+                void* outs[mrt::kTileMaxSteps];
+                for (int k = 0; k < m; ++k) outs[k] = const_cast<void*>(state(seg, j + k));
+                const hipError_t e = mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
+                                                 c->tile_form.steps, m, false, state(seg, j - 1), nullptr, outs,
+                                                 c->d_health, st);
+                if (e != hipSuccess) return e;
+                j += m;
+            }
+            return hipSuccess;
+        }
         for (int j = 1; j < stop - start; ++j) {
             const hipError_t e = mrt::k_step(c->prec, c->d_inst, c->d_items, c->nitems, state(seg, j - 1),
                                              const_cast<void*>(state(seg, j)), c->d_health, c->grid, c->nt,

@@ -1101,17 +1101,29 @@ __device__ __forceinline__ void adjoint_block(ConstInst* __restrict__ P, int ite
     }
     // wave reduction of the 12 non-trivial rate gradients, then the four
     // waves' sums in a fixed order into the item's partial row
+    // Halving: each stage a lane keeps half of its values, those its bit of the
+    // lane number names, and gives the other half to its partner, so the twelve
+    // sums over 64 lanes take 14 exchanges instead of 72 (the same additions in
+    // the same tree: bitwise the same sums).  Lane l ends with sum l / 4.
+    double v[16];
 #pragma unroll
-    for (int k = 4; k < 16; ++k) {
-        double v = acc[k];
+    for (int k = 0; k < 16; ++k) v[k] = k < 12 ? acc[k + 4] : 0.0;
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-        acc[k] = v;
+    for (int half = 8, off = 32; half >= 1; half >>= 1, off >>= 1) {
+        const bool upper = lane & off;
+#pragma unroll
+        for (int j = 0; j < half; ++j) {
+            if (half == 8 && j >= 4) {               // sums 4..7 of the lower lanes; the upper ones' are padding
+                v[j] = v[j] + __shfl_xor(v[j], off, 64);
+                continue;
+            }
+            const double give = upper ? v[j] : v[j + half], keep = upper ? v[j + half] : v[j];
+            v[j] = keep + __shfl_xor(give, off, 64);
+        }
     }
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 4; k < 16; ++k) red[wv][k - 4] = acc[k];
-    }
+    v[0] += __shfl_xor(v[0], 2, 64);
+    v[0] += __shfl_xor(v[0], 1, 64);
+    if ((lane & 3) == 0 && lane < 48) red[wv][lane >> 2] = v[0];
     __syncthreads();
     if (wv == 0 && lane < 16) {
         double* row = &partial[(long long)item * 16];
@@ -1717,12 +1729,19 @@ struct TileRows {
     S v[kBuffers][NR][16 * 64 + 2];
 };
 
+// Step k + 1 of the launch goes to outs.f[k] where that is not NULL (the last
+// always; every one when a gradient's states are recomputed).
+template <typename S>
+struct TileOuts {
+    S* f[kTileMaxSteps];
+};
+
 // WALLS: the grid has reflecting sides (their code costs registers: FP64 then
-// runs blocks of eight rows only, 202 VGPRs).
+// runs blocks of eight rows only, 179 VGPRs).
 template <typename S, typename C, bool COMP, int NR, bool WALLS>
 __global__ __launch_bounds__(64 * NR, (NR == 16 ? 4 : NR == 8 && WALLS && sizeof(S) == 8 ? 2 : 3)) void tile_kernel(
         const Inst* __restrict__ insts, const Item* __restrict__ items, int nitems, int overlap, int steps,
-        const S* __restrict__ fin, S* __restrict__ fout, unsigned* __restrict__ health) {
+        const S* __restrict__ fin, TileOuts<S> outs, unsigned* __restrict__ health) {
     __shared__ TileRows<S, NR> lds;
     ConstItem* citems = (ConstItem*)items;
     // XCD-aware item order as in step_kernel
@@ -1781,6 +1800,8 @@ __global__ __launch_bounds__(64 * NR, (NR == 16 ? 4 : NR == 8 && WALLS && sizeof
         return base + ((unsigned long long)(unsigned(P->origin) + unsigned(r) * unsigned(P->pitch)) - 1u) * sizeof(S);
     };
     const unsigned bcx = unsigned(xs + 1) * unsigned(sizeof(S));
+    const bool stored = lane >= overlap && lane < 64 - overlap && row >= overlap && row < NR - overlap &&
+                        x < nx && y < ny;
     bool healthy = true;
 
     S f[16];
@@ -1858,14 +1879,15 @@ __global__ __launch_bounds__(64 * NR, (NR == 16 ? 4 : NR == 8 && WALLS && sizeof
                            y >= 0 && y < ny;
         healthy = healthy && (!valid || (rho > C(0) && Pp > C(0)));
         if constexpr (kBuffers == 1) __syncthreads();
-    }
-    if (lane >= overlap && lane < 64 - overlap && row >= overlap && row < NR - overlap && x < nx && y < ny) {
-        unsigned long long a = row_at(reinterpret_cast<unsigned long long>(fout + P->off), y);
-        const unsigned bo = lane_off(bcx);
+        S* out = outs.f[k];
+        if (out && stored) {
+            unsigned long long a = row_at(reinterpret_cast<unsigned long long>(out + P->off), y);
+            const unsigned bo = lane_off(bcx);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            gstore<S, false>(a, bo, f[i]);
-            if (i < 15) a = next_pop(a, pstep);
+            for (int i = 0; i < 16; ++i) {
+                gstore<S, false>(a, bo, f[i]);
+                if (i < 15) a = next_pop(a, pstep);
+            }
         }
     }
     if (!healthy) atomicOr(health, 1u);
@@ -2240,15 +2262,20 @@ hipError_t k_tube(int prec, const Inst* insts, const Item* items, int nitems, in
 // `steps` <= overlap steps from fin to fout by the tile march (`rows` = 8, 12
 // or 16 rows a block; the items are tile_width(overlap) columns of
 // tile_height(rows, overlap) rows); no ghosts are read.  walls: the grid has
-// reflecting sides (FP64: rows = 8 then, and never 16).
+// reflecting sides (FP64: rows = 8 then, and never 16).  fouts: NULL (the last
+// step goes to fout), or `steps` buffers, one for each step.
 template <typename S, typename C, bool COMP>
 hipError_t launch_tile(const Inst* insts, const Item* items, int nitems, int rows, int overlap, int steps,
-                       bool walls, const void* fin, void* fout, unsigned* health, hipStream_t st) {
+                       bool walls, const void* fin, void* fout, void* const* fouts, unsigned* health,
+                       hipStream_t st) {
     if (nitems <= 0) return hipSuccess;
-    if (steps < 1 || steps > overlap || tile_height(rows, overlap) < 1) return hipErrorInvalidValue;
+    if (steps < 1 || steps > overlap || overlap > kTileMaxSteps || tile_height(rows, overlap) < 1) return hipErrorInvalidValue;
     const dim3 blocks(8 * ((nitems + 7) / 8)), threads(64 * rows);
     const S* in = static_cast<const S*>(fin);
-    S* out = static_cast<S*>(fout);
+    TileOuts<S> out;
+    for (int k = 0; k < kTileMaxSteps; ++k)
+        out.f[k] = k < steps && fouts ? static_cast<S*>(fouts[k]) : nullptr;
+    if (!fouts) out.f[steps - 1] = static_cast<S*>(fout);
 #define MRT_TILE(NR, WALLS) \
     hipLaunchKernelGGL((tile_kernel<S, C, COMP, NR, WALLS>), blocks, threads, 0, st, insts, items, nitems, overlap, steps, in, out, health)
     if (walls && rows == 8) {
@@ -2272,11 +2299,12 @@ hipError_t launch_tile(const Inst* insts, const Item* items, int nitems, int row
 }
 
 hipError_t k_tile(int prec, const Inst* insts, const Item* items, int nitems, int rows, int overlap,
-                  int steps, bool walls, const void* fin, void* fout, unsigned* health, hipStream_t st) {
+                  int steps, bool walls, const void* fin, void* fout, void* const* fouts, unsigned* health,
+                  hipStream_t st) {
     switch (prec) {
-        case 0: return launch_tile<double, double, false>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, health, st);
-        case 1: return launch_tile<float, float, true>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, health, st);
-        case 2: return launch_tile<float, double, false>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, health, st);
+        case 0: return launch_tile<double, double, false>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, fouts, health, st);
+        case 1: return launch_tile<float, float, true>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, fouts, health, st);
+        case 2: return launch_tile<float, double, false>(insts, items, nitems, rows, overlap, steps, walls, fin, fout, fouts, health, st);
         default: return hipErrorInvalidValue;
     }
 }
