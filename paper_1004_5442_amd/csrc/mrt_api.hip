@@ -398,27 +398,30 @@ PipeShape pipe_shape(int nx, int ny, int prec, int rows) {
 
 // Launch shape of the tile march: rows per block and steps per launch (the
 // overlap recomputed on every side), and its expected microseconds per step: a
-// launch's start, and per step the longer of one wave's chain of dependent
-// instructions and the resident waves' throughput.  A reflecting side lengthens
+// launch's start (and that of further rounds of blocks), and per step the longer
+// of one wave's chain of dependent instructions and the waves' throughput.  A reflecting side lengthens
 // the chain of the blocks at it.  Measured per step, FP32 with FP64 collision:
 // 256^2 periodic 12 rows x 3 steps 3.5 us, 16 x 4 3.7, 8 x 2 4.6, 12 x 4 (more
 // blocks than CUs) 5.6, the one-step kernel 4.6; 360 x 100 with a wall 8 x 2 4.5,
-// 12 x 4 4.6, 12 x 3 5.0, one step 5.3.
+// 12 x 4 4.5, 12 x 3 4.8, one step 5.3; FP64 256^2 12 x 3 4.3, 8 x 2 5.6, one step
+// 6.2; 400 x 300 (two rounds) 12 x 3 7.8, as the pipeline; 500^2 12.1 against the
+// pipeline's 10.2.
 struct TileShape {
     int rows = 8, steps = 1;
     double us = -1;
 };
 TileShape tile_shape(int nx, int ny, int prec, const int bc[4]) {
     const bool fp64 = prec == MRT_FP64, walls = has_kind(bc, MRT_BC_REFLECT);
-    const double start = 4.0, chain = 1.4, wave = fp64 ? 1.05 : 0.69, wall = walls ? 0.9 : 0.0;
-    const int most = !fp64 ? 16 : walls ? 8 : 12;
+    const double start = 4.0, chain = 1.4, wave = fp64 ? 1.0 : 0.69, wall = walls ? 0.9 : 0.0;
+    const int most = fp64 ? 12 : 16;
     TileShape best;
     for (int rows = 8; rows <= most; rows += 4)
         for (int steps = 2; steps <= mrt::kTileMaxSteps && 2 * steps < rows; ++steps) {
             const int w = mrt::tile_width(steps), h = mrt::tile_height(rows, steps);
             const double blocks = double((nx + w - 1) / w) * ((ny + h - 1) / h);
-            const double level = std::max(chain, std::ceil(blocks / 256.0) * rows / 4.0 * wave) + wall;
-            const double us = (start + steps * level) / steps;
+            const double rounds = std::ceil(blocks / 256.0);
+            const double level = std::max(chain, rounds * rows / 4.0 * wave) + wall;
+            const double us = (start + 1.5 * (rounds - 1) + steps * level) / steps;
             if (best.us < 0 || us < best.us) best = TileShape{rows, steps, us};
         }
     return best;
@@ -429,17 +432,19 @@ TileShape tile_shape(int nx, int ny, int prec, const int bc[4]) {
 // (per_pass 1 or 2), the level pipeline (cost row iterations for four steps)
 // and the tile march.  Microseconds of one iteration and site updates per
 // microsecond as measured (FP64, FP32, FP32 with FP64 collision); the one-step
-// kernel adds its launch.  Measured per step, other form -> pipeline: FP64
+// kernel adds its launch, and reflecting sides lengthen it.  Measured per step, other form -> pipeline: FP64
 // 360 x 100 5.6 -> 5.9 (stays), 400 x 300 11.4 -> 7.8, 512^2 15.4 -> 10.8,
 // 1024^2 39.3 -> 22.9, 4096^2 575 -> 282; FP32 with FP64 collision 512^2 9.4 ->
 // 10.2 (stays), 700^2 16.2 -> 12.4, 1024^2 22.2 -> 19.3, 4096^2 279 -> 198;
 // FP32 512^2 9.9 -> 10.1 (stays), 700^2 17.2 -> 12.1, 4096^2 312 -> 205.
 enum class Form { Steps, Pipe, Tile };
-Form default_form(int nx, int ny, int prec, int per_pass, const PipeShape& pipe, const TileShape& tile) {
+Form default_form(int nx, int ny, int prec, const int bc[4], int per_pass, const PipeShape& pipe,
+                  const TileShape& tile) {
     const double iteration[3] = {2.0, 2.4, 2.45};
     const double rate1[3] = {18500, 33000, 35000}, rate2[3] = {28000, 53000, 54000};
     const double cells = (double)nx * ny;
-    const double steps = per_pass == 2 ? cells / rate2[prec] : std::max(4.3, 2.2 + cells / rate1[prec]);
+    const double walls = has_kind(bc, MRT_BC_REFLECT) ? 1.5 : 0.0;
+    const double steps = per_pass == 2 ? cells / rate2[prec] : std::max(4.3, 2.2 + cells / rate1[prec]) + walls;
     const double piped = pipe.cost * iteration[prec] / kPipeSteps;
     if (tile.us < steps && tile.us < piped) return Form::Tile;
     return piped < steps ? Form::Pipe : Form::Steps;
@@ -804,7 +809,7 @@ int mrt_init_grid(mrt_ctx** out, int nx, int ny, int precision, const int bc[4],
     } else {
         const PipeShape pipe = pipe_shape(nx, ny, precision, 0);
         const TileShape tile = tile_shape(nx, ny, precision, bc);
-        const Form form = default_form(nx, ny, precision, c->per_pass, pipe, tile);
+        const Form form = default_form(nx, ny, precision, bc, c->per_pass, pipe, tile);
         if (form == Form::Pipe) {
             if (build_items_pipe(c, pipe) != MRT_OK) return fail(MRT_EDEVICE);
             c->pipe = true;
