@@ -542,6 +542,7 @@ struct mrt_ctx {
     int nitems_t = 0;
     GraphCache graphs_t;             // captured tile-march passes
     bool ghosts_stale = false;       // reflecting-wall ghosts of the current state (the pipeline and the tile march write none)
+    bool recorded = false;           // passes of those forms are in a graph of the caller's: its replays leave them stale unseen
     bool eager = false;              // launch step by step (the tile autotuner)
     int scheme = 0;                  // MRT_SCHEME_* flags
     void* f_tmp = nullptr;           // post-collision state of the split scheme
@@ -881,6 +882,15 @@ int mrt_step(mrt_ctx* c, int n) { return step_impl(c, n, true); }
 
 int mrt_prepare_steps(mrt_ctx* c, int n) { return step_impl(c, n, false); }
 
+static bool is_recording(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
 static int step_impl(mrt_ctx* c, int n, bool launch) {
     if (!c) return MRT_EINVAL;
     std::string& ctx_err = c->err;
@@ -889,6 +899,8 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
     const int perim = 2 * (c->nx + c->ny);
     const bool reflect = has_kind(c->bc, MRT_BC_REFLECT);
     const bool xwall = c->bc[0] == MRT_BC_REFLECT || c->bc[1] == MRT_BC_REFLECT;
+    // a caller's graph may be replayed on a state of another form
+    const bool recording = launch && reflect && is_recording(c->stream);
     if (c->pipe && c->scheme == 0 && n >= kPipeSteps) {
         // the level pipeline, four steps a pass; the remaining steps by the
         // forms below.  It forms the y-wall ghosts itself and reads those of
@@ -912,6 +924,7 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
             HIPTRY(run_graphs(c->graphs_p, c->cur, passes, c->stream, enqueue_p, launch));
         }
         if (launch) c->ghosts_stale = reflect;
+        c->recorded |= recording;
         n -= passes * kPipeSteps;
         if (n == 0) return MRT_OK;
     }
@@ -940,13 +953,14 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
             c->cur ^= 1;
         }
         if (launch && n) c->ghosts_stale = reflect;
+        c->recorded |= recording;
         return MRT_OK;
     }
     // the one-step kernel that keeps the wall ghosts itself expects them
     // current; the other forms refill them
-    if (launch && c->ghosts_stale && c->per_pass == 1 && c->scheme == 0) {
+    if (launch && n && (c->ghosts_stale || c->recorded || recording) && c->per_pass == 1 && c->scheme == 0) {
         HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, perim, c->f[c->cur], 1, c->stream));
-        c->ghosts_stale = false;
+        if (!recording) c->ghosts_stale = false;
     }
     // one step reading buffer `cur`: reflecting-wall ghosts unless the step
     // kernel wrote them with the previous step's output (c->walls), then the
@@ -1515,6 +1529,8 @@ int mrt_step_checkpointed(mrt_ctx* c, void* f, void* f_tmp, int segment, int nst
         a = dst;
     }
     if (a != f) HIPTRY(hipMemcpyAsync(f, a, bytes, hipMemcpyDeviceToDevice, c->stream));
+    // f may be the context's own buffer
+    if (c->tile || c->pipe) c->ghosts_stale = reflect;
     return MRT_OK;
 }
 

@@ -108,3 +108,26 @@ def test_pipeline_reports_an_unhealthy_state(prec):
     with pytest.raises(UnstableError):
         s.sync()
     s.close()
+
+
+def test_walls_after_a_checkpointed_run_in_the_contexts_buffers():
+    """The multi-step forms leave the wall ghosts of an explicit buffer
+    unwritten; the one-step kernel that expects them gets them all the same
+    when that buffer is the context's own."""
+    from ctypes import c_void_p
+
+    from paper_1004_5442_amd import lib as L
+    case = smooth_case(90, 30, ("reflect", "reflect", "reflect", "reflect"), seed=4)
+    print(f"case {case.name} checkpointed run in the context's buffers", flush=True)
+    s = solver_for_case(case, "fp32_eq64")
+    s.set_pipeline(0)
+    ck = s.empty_state()
+    cur, other = s.buffers()
+    assert L.raw().mrt_step_checkpointed(s._h, c_void_p(cur), c_void_p(other), 8, 8,
+                                         (c_void_p * 1)(ck.data_ptr())) == 0
+    s.set_steps_per_pass(1, 0)
+    s.step(3)
+    want, p = oracle_run(case, 11)
+    err = field_errors(s.moments(), mrt.macroscopic(want, p.b))
+    assert max(err.values()) < 1e-5, err
+    s.close()
