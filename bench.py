@@ -6,11 +6,11 @@ One "step" is one time step of the whole hot path (ghosts, moments,
 equilibrium, M / relax / Minv collision, Lax-Wendroff convection, forward
 Euler) over the whole grid of the headline workload: the 4096 x 4096 Mach-5
 shock hitting a dense bubble, FP32 populations with FP64 collision
-(MRT_FP32_EQ64), run as the library runs it by default at this size: two
-time steps per kernel pass (32-row bands).  value = MLUPS (million
+(MRT_FP32_EQ64), run as the library runs it by default at this size: four
+time steps per kernel pass (the level pipeline).  value = MLUPS (million
 lattice-site updates per second), populations already resident in HBM.
-Extra fields report the one-step-per-pass kernel and the FP64 form on the
-same grid, the 1024^2 2D Riemann problem, the batched shock tubes and the
+Extra fields report the two- and one-step-per-pass kernels and the FP64 form on
+the same grid, the 1024^2 2D Riemann problem, the batched shock tubes and the
 adjoint step, the roofline of the step kernel, and the oracle's CPU rate on a
 bounded sample.  Prints one JSON line.
 """
@@ -27,9 +27,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0               # MI355X HBM3E, published
 BYTES_PER_SITE = {"fp64": 256, "fp32": 128, "fp32_eq64": 128}   # 16 reads + 16 writes
-HEADLINE_PER_PASS = 2               # time steps per kernel pass (the default at this size)
-HEADLINE_BAND_ROWS = 32             # band height of the two-step kernel (the default here)
-FP64_BAND_ROWS = 64                 # the same for FP64 storage (one block per CU)
+HEADLINE_PER_PASS = 4               # time steps per kernel pass (the default at this size)
+HEADLINE_BAND_ROWS = 32             # band height of the two-step kernel (its default here)
 HEADLINE_TILE_ROWS = 8              # the one-step kernel's band height for this grid
 
 # HBM traffic of one step2_kernel launch (two steps) on the headline
@@ -150,7 +149,7 @@ def _configured_solver(case, precision, autotune, tile_rows, scheme, per_pass):
     elif tile_rows:
         s.set_steps_per_pass(1, 0)
         s.set_tile(tile_rows)
-    elif autotune:
+    elif autotune and not per_pass:
         s.autotune(4)
     return s
 
@@ -158,14 +157,15 @@ def _configured_solver(case, precision, autotune, tile_rows, scheme, per_pass):
 def time_solver(case, precision, steps, warmup, autotune=True, tile_rows=0, scheme=None,
                 per_pass=0):
     """per_pass 1 or 2 with tile_rows: that kernel and band height; else the
-    autotuner's choice (autotune) or the library's default."""
+    autotuner's choice (autotune) or the library's default (per_pass 4, or 0
+    without autotune)."""
     import torch
     s = _configured_solver(case, precision, autotune, tile_rows, scheme, per_pass)
     heat = _configured_solver(case, precision, False, tile_rows, scheme, per_pass)
     if autotune and not tile_rows and not per_pass:
         heat.set_tile(*s.tile())
         k, r = s.steps_per_pass()
-        if not scheme:
+        if not scheme and s.pipeline() < 0:
             heat.set_steps_per_pass(k, r if k == 2 else 0)
     pre = _preheat(heat.step, max_steps=case.nsteps)
     heat.close()
@@ -177,6 +177,8 @@ def time_solver(case, precision, steps, warmup, autotune=True, tile_rows=0, sche
     s.sync()      # raises if the run went unhealthy
     tile = s.tile()
     pp = s.steps_per_pass()
+    if s.pipeline() > 0:
+        pp = (4, s.pipeline())       # the level pipeline (what remains of a step count: pp)
     s.close()
     mlups = case.cells * steps / sec / 1e6
     return {"mlups": mlups, "sec": sec, "ms_per_step": 1e3 * sec / steps, "tile": tile,
@@ -346,11 +348,15 @@ def roofline(case, precision, r, traffic=None):
     out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
            "traffic_unit": "bytes per launch", "algorithmic_bytes": per_launch_bytes,
-           "kernel": "step2_kernel" if per_pass == 2 else "step_kernel",
+           "kernel": {4: "pipe_kernel", 2: "step2_kernel"}.get(per_pass, "step_kernel"),
            "bytes_per_site": BYTES_PER_SITE[precision], "site_updates_per_launch": case.cells * per_pass}
     if traffic is not None:
         # what the launch really moves, per second (counter readings)
         out["traffic_GBs"] = round(traffic / (r["sec"] / r["steps"] * per_pass) / 1e9, 1)
+    if per_pass == 4:
+        out["note"] = ("four time steps per launch: the state crosses the memory interface once per "
+                       "launch, about 0.28 x the per-step algorithmic bytes; bound by vector "
+                       "instructions (FP32 storage) or by that traffic (FP64)")
     if per_pass == 2:
         out["note"] = ("two time steps per launch: each launch reads f^n once and writes f^{n+2}, so "
                        "its HBM traffic (traffic_GBs) is about 0.61 x the per-step algorithmic bytes; "
@@ -462,12 +468,18 @@ def extra_legs(head, prec, steps):
         return {"mlups": round(r1["mlups"], 1), "band_rows": HEADLINE_TILE_ROWS,
                 "roofline_frac": roofline(head, prec, r1)["frac"]}
 
+    def two_step():
+        r2 = time_solver(head, prec, k, 3, tile_rows=HEADLINE_BAND_ROWS, per_pass=2)
+        r2["steps"] = k
+        return {"mlups": round(r2["mlups"], 1), "band_rows": HEADLINE_BAND_ROWS,
+                "roofline_frac": roofline(head, prec, r2)["frac"]}
+
     def fp64():
-        # the library's default at this size: two steps per pass, 64-row bands
-        r64 = time_solver(head, "fp64", k, 3, tile_rows=FP64_BAND_ROWS, per_pass=2)
+        # the library's default at this size
+        r64 = time_solver(head, "fp64", k, 3, per_pass=4)
         r64["steps"] = k
-        return {"mlups": round(r64["mlups"], 1), "steps_per_pass": 2, "band_rows": FP64_BAND_ROWS,
-                "roofline_frac": roofline(head, "fp64", r64)["frac"]}
+        return {"mlups": round(r64["mlups"], 1), "steps_per_pass": r64["per_pass"],
+                "band_rows": r64["band_rows"], "roofline_frac": roofline(head, "fp64", r64)["frac"]}
 
     def fp64_one_step():
         r64 = time_solver(head, "fp64", k, 3, tile_rows=HEADLINE_TILE_ROWS)
@@ -476,9 +488,9 @@ def extra_legs(head, prec, steps):
                 "roofline_frac": roofline(head, "fp64", r64)["frac"]}
 
     def fp32():
-        r32 = time_solver(head, "fp32", k, 3, tile_rows=HEADLINE_BAND_ROWS, per_pass=2)
+        r32 = time_solver(head, "fp32", k, 3, per_pass=4)
         r32["steps"] = k
-        return {"mlups": round(r32["mlups"], 1), "steps_per_pass": 2,
+        return {"mlups": round(r32["mlups"], 1), "steps_per_pass": r32["per_pass"],
                 "roofline_frac": roofline(head, "fp32", r32)["frac"]}
 
     def riemann(pr):
@@ -544,6 +556,7 @@ def extra_legs(head, prec, steps):
 
     return {
         "device_copy_1gib": device_copy,
+        "fp32_eq64_two_steps_per_pass": two_step,
         "fp32_eq64_one_step_per_pass": one_step,
         "fp64_same_grid": fp64,
         "fp64_one_step_per_pass": fp64_one_step,
@@ -570,11 +583,12 @@ def main():
     ap.add_argument("--warmup", type=int, default=10)
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--no-extra", action="store_true")
-    ap.add_argument("--steps-per-pass", type=int, default=HEADLINE_PER_PASS, choices=(1, 2),
-                    help="kernel of the headline run: two time steps per pass or one")
+    ap.add_argument("--steps-per-pass", type=int, default=HEADLINE_PER_PASS, choices=(1, 2, 4),
+                    help="kernel of the headline run: four time steps per pass (the library's "
+                         "default), two or one")
     ap.add_argument("--rows", type=int, default=0,
-                    help="band height of the headline run (default: 32 for two steps per "
-                         "pass, 8 for one)")
+                    help="band height of the headline run with two steps per pass (default 32) "
+                         "or one (8)")
     ap.add_argument("--only", default=None,
                     help="run only this extra measurement (a key of 'extra') and print its "
                          "JSON object: for profiling one kernel")
@@ -606,7 +620,8 @@ def main():
             sys.exit(f"--only: one of {sorted(legs)}")
         print(json.dumps({"leg": args.only, **legs[args.only]()}), flush=True)
         return
-    rows = args.rows or (HEADLINE_BAND_ROWS if args.steps_per_pass == 2 else HEADLINE_TILE_ROWS)
+    rows = 0 if args.steps_per_pass == 4 else args.rows or (
+        HEADLINE_BAND_ROWS if args.steps_per_pass == 2 else HEADLINE_TILE_ROWS)
     r = time_solver(head, prec, args.steps, args.warmup, tile_rows=rows, per_pass=args.steps_per_pass)
     r["steps"] = args.steps
     out = {

@@ -127,9 +127,12 @@ int mrt_set_fields(mrt_ctx* ctx, const double* rho, const double* ux, const doub
                    const double* T, int on_device);
 
 /* Advance n time steps (Eq. 3, forward Euler, Lax-Wendroff).  Asynchronous.
- * One kernel pass per step, or per two steps (mrt_set_steps_per_pass; the
- * default from about 1024 x 1024 cells on), an odd
- * last step then taking a one-step pass.  Health (NaN, rho <= 0, T <= 0) is
+ * One kernel pass per several steps: by default the tube march on shock tubes
+ * (up to 24 steps; mrt_set_steps_per_pass), else the form expected to take
+ * the least time of the level pipeline (4 steps; mrt_set_pipeline), the tile
+ * march (2 to 6 steps, a block holding 8, 12 or 16 rows of 64 columns with
+ * the overlap recomputed; small grids) and one or two steps per pass.  Steps
+ * left over take a shorter pass.  Health (NaN, rho <= 0, T <= 0) is
  * recorded on the device and reported by the next synchronising call.
  * Errors: MRT_ESTATE, MRT_EINVAL (n < 0). */
 int mrt_step(mrt_ctx* ctx, int n);
@@ -138,10 +141,10 @@ int mrt_step(mrt_ctx* ctx, int n);
  * graphs that a following mrt_step(ctx, n) will replay, so that their
  * one-time capture, instantiation and upload cost (about a millisecond for
  * 64 passes) falls outside a timed region or a latency-critical loop.  The
- * kernel passes of mrt_step(n) (n, or n / 2 with two steps per pass) are
+ * kernel passes of mrt_step(n) (n over the steps of a pass) are
  * replayed as replays of one 64-pass graph and one graph of the remaining
- * passes, per start buffer (an odd step of the two-step mode is launched
- * directly); the graphs are kept until the tile, steps per pass, scheme or
+ * passes, per start buffer (the steps left over that make no whole pass are
+ * launched directly); the graphs are kept until the tile, steps per pass, scheme or
  * context changes.  Launches no kernel (the uploads are enqueued on the
  * context's stream); errors as mrt_step. */
 int mrt_prepare_steps(mrt_ctx* ctx, int n);
@@ -179,11 +182,14 @@ int mrt_sync(mrt_ctx* ctx);
 int mrt_set_tile(mrt_ctx* ctx, int rows_per_item, int grid_blocks);
 int mrt_get_tile(const mrt_ctx* ctx, int* rows_per_item, int* grid_blocks);
 
-/* Time steps per pass over the populations: 1, 2 or 4 (default: 4 for the
+/* Time steps per pass over the populations: 1, 2 or 4; names the form that
+ * runs, in place of the level pipeline and the tile march.  Without them the
+ * default is 4 for the
  * grids the tube march below covers; 2 for grids whose population buffer
  * exceeds the 256 MB last-level cache or that give at least 512 two-step
- * work items of 8-row bands, about 1024 x 1024 cells and up; else 1.
- * mrt_autotune times all that apply and keeps the fastest).  With 2, one kernel launch
+ * work items of 8-row bands, about 1024 x 1024 cells and up; else 1 (also
+ * what mrt_get_steps_per_pass gives while they run).
+ * mrt_autotune times all that apply and keeps the fastest.  With 2, one kernel launch
  * advances the state two steps of Eq. 3 (the same per-site arithmetic as two
  * single steps, f^{n+1} rounded to the storage precision as a stored state
  * would be, so the same result up to rounding order: measured bit-identical
@@ -219,10 +225,11 @@ int mrt_get_steps_per_pass(const mrt_ctx* ctx, int* steps, int* rows);
  * remaining steps by the form of mrt_set_steps_per_pass.  Results equal single
  * steps to rounding order (bit-identical in the FP32 storage forms, as
  * measured).  rows: band height (0: by grid size), -1 turns it off.
- * mrt_init_grid turns it on where it is expected to be faster (from about
- * 400 x 300 cells on in FP64, 600^2 in FP32 storage; not on the tube march's
- * grids); mrt_autotune times it too, and mrt_set_steps_per_pass, which names
- * another form, turns it off.
+ * mrt_init_grid turns it on where it is expected to be faster than the tile
+ * march and than one or two steps per pass (from about 400 x 300 cells on in
+ * FP64, 600^2 in FP32 storage; not on the tube march's grids); mrt_autotune
+ * times them all, and mrt_set_steps_per_pass, which names another form, turns
+ * it off.  Turning it on or off also ends the tile march.
  * mrt_get_pipeline gives the band height, -1 when off.  Errors: MRT_EINVAL
  * (rows < -1). */
 int mrt_set_pipeline(mrt_ctx* ctx, int rows);
@@ -248,8 +255,9 @@ int mrt_get_pipeline(const mrt_ctx* ctx, int* rows);
 int mrt_set_scheme(mrt_ctx* ctx, int flags);
 
 /* Time candidate launches on the current state (the populations are saved
- * and restored): one-step tiles (rows 1..128, grid sizes) and two steps per
- * pass with bands of 8, 16 and 32 rows; keep the fastest per step.
+ * and restored): one-step tiles (rows 1..128, grid sizes), two steps per
+ * pass with bands of 8, 16 and 32 rows, and the tube, tile and pipeline forms
+ * where they apply; keep the fastest per step.
  * Synchronises. */
 int mrt_autotune(mrt_ctx* ctx, int steps_per_trial);
 
