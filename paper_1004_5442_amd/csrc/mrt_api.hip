@@ -542,7 +542,7 @@ struct mrt_ctx {
     int nitems_t = 0;
     GraphCache graphs_t;             // captured tile-march passes
     bool ghosts_stale = false;       // reflecting-wall ghosts of the current state (the pipeline and the tile march write none)
-    bool recorded = false;           // passes of those forms are in a graph of the caller's: its replays leave them stale unseen
+    bool recorded = false;           // such passes (mrt_step, mrt_step_checkpointed) are in a graph of the caller's: its replays leave them stale unseen
     bool eager = false;              // launch step by step (the tile autotuner)
     int scheme = 0;                  // MRT_SCHEME_* flags
     void* f_tmp = nullptr;           // post-collision state of the split scheme
@@ -570,6 +570,16 @@ int ctx_fail(mrt_ctx* c, int code, const std::string& msg) {
     return code;
 }
 
+// Whether the caller is recording the stream into a graph of its own.
+bool is_recording(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
 // Ghost ring after the state was set from outside a step: the equilibrium
 // ghosts of MRT_BC_EQ sides into every population buffer (no step overwrites
 // them) and the reflecting-wall ghosts of the current state (from then on
@@ -583,7 +593,8 @@ int fill_ghosts(mrt_ctx* c) {
     }
     if (has_kind(c->bc, MRT_BC_REFLECT))
         HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, perim, c->f[c->cur], 1, c->stream));
-    c->ghosts_stale = false;
+    // launches that are only being recorded have written nothing yet
+    if (!is_recording(c->stream)) c->ghosts_stale = false;
     return MRT_OK;
 }
 
@@ -881,15 +892,6 @@ static int step_impl(mrt_ctx* c, int n, bool launch);
 int mrt_step(mrt_ctx* c, int n) { return step_impl(c, n, true); }
 
 int mrt_prepare_steps(mrt_ctx* c, int n) { return step_impl(c, n, false); }
-
-static bool is_recording(hipStream_t stream) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return status == hipStreamCaptureStatusActive;
-}
 
 static int step_impl(mrt_ctx* c, int n, bool launch) {
     if (!c) return MRT_EINVAL;
@@ -1530,7 +1532,10 @@ int mrt_step_checkpointed(mrt_ctx* c, void* f, void* f_tmp, int segment, int nst
     }
     if (a != f) HIPTRY(hipMemcpyAsync(f, a, bytes, hipMemcpyDeviceToDevice, c->stream));
     // f may be the context's own buffer
-    if (c->tile || c->pipe) c->ghosts_stale = reflect;
+    if (c->tile || c->pipe) {
+        c->ghosts_stale = reflect;
+        c->recorded |= reflect && is_recording(c->stream);
+    }
     return MRT_OK;
 }
 

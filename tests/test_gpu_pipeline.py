@@ -131,3 +131,64 @@ def test_walls_after_a_checkpointed_run_in_the_contexts_buffers():
     err = field_errors(s.moments(), mrt.macroscopic(want, p.b))
     assert max(err.values()) < 1e-5, err
     s.close()
+
+
+@pytest.mark.parametrize("form", ["pipeline", "tile"])
+def test_walls_after_a_recorded_checkpointed_run(form):
+    """A checkpointed run on the context's own buffers recorded into a graph
+    of the caller's: its replays leave the wall ghosts unwritten after the
+    context has refilled them, and the one-step kernel still reads those of
+    the current state, after every replay."""
+    from ctypes import c_void_p
+
+    from paper_1004_5442_amd import lib as L
+    case = smooth_case(90, 30, ("reflect", "reflect", "reflect", "reflect"), seed=4)
+    print(f"case {case.name} {form} recorded checkpointed run", flush=True)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s = solver_for_case(case, "fp64", stream=st)
+        if form == "pipeline":
+            s.set_pipeline(0)
+        ck = s.empty_state()
+        cur, other = s.buffers()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            assert L.raw().mrt_step_checkpointed(s._h, c_void_p(cur), c_void_p(other), 8, 8,
+                                                 (c_void_p * 1)(ck.data_ptr())) == 0
+        s.set_steps_per_pass(1, 0)
+        for k in (1, 2):
+            graph.replay()
+            s.step(2)                     # an even count: the current buffer stays the recorded one
+            want, _ = oracle_run(case, 10 * k)
+            got = s.populations()
+            assert np.max(np.abs(got - want)) <= 1e-12 * np.abs(want).max(), k
+        s.close()
+
+
+def test_walls_after_fields_that_were_only_recorded():
+    """Recording mrt_set_fields writes nothing yet: wall ghosts that a
+    multi-step pass left stale are still renewed before the one-step kernel
+    reads them."""
+    case = smooth_case(90, 30, ("reflect", "reflect", "reflect", "reflect"), seed=4)
+    print(f"case {case.name} recorded fields", flush=True)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s = solver_for_case(case, "fp64", stream=st)
+        s.set_pipeline(0)
+        s.step(8)
+        s.set_pipeline(-1)
+        fields = [torch.tensor(np.ascontiguousarray(a), device="cuda")
+                  for a in (case.rho, case.ux, case.uy, case.T)]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        from ctypes import c_void_p
+
+        from paper_1004_5442_amd import lib as L
+        with torch.cuda.graph(graph, stream=st):
+            assert L.raw().mrt_set_fields(s._h, *[c_void_p(t.data_ptr()) for t in fields], 1) == 0
+        s.step(3)
+        want, _ = oracle_run(case, 11)
+        got = s.populations()
+        assert np.max(np.abs(got - want)) <= 1e-12 * np.abs(want).max()
+        s.close()
