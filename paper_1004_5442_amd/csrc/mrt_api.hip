@@ -542,7 +542,7 @@ struct mrt_ctx {
     int nitems_t = 0;
     GraphCache graphs_t;             // captured tile-march passes
     bool ghosts_stale = false;       // reflecting-wall ghosts of the current state (the pipeline and the tile march write none)
-    bool recorded = false;           // such passes (mrt_step, mrt_step_checkpointed) are in a graph of the caller's: its replays leave them stale unseen
+    bool recorded = false;           // passes of those forms are in a graph of the caller's: its replays leave them stale unseen
     bool eager = false;              // launch step by step (the tile autotuner)
     int scheme = 0;                  // MRT_SCHEME_* flags
     void* f_tmp = nullptr;           // post-collision state of the split scheme
@@ -1518,6 +1518,9 @@ int mrt_step_checkpointed(mrt_ctx* c, void* f, void* f_tmp, int segment, int nst
         else
             dst = a == f ? f_tmp : f;
         if (c->tile) {
+            // the tile march reads no ghosts, but a checkpoint keeps its ring
+            if (ring && a != f && a != f_tmp)
+                HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, 2 * (c->nx + c->ny), a, 3, c->stream));
             HIPTRY(mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
                                c->tile_form.steps, m, reflect, a, dst, nullptr, c->d_health, c->stream));
         } else if (m == kPipeSteps) {
@@ -1531,11 +1534,11 @@ int mrt_step_checkpointed(mrt_ctx* c, void* f, void* f_tmp, int segment, int nst
         a = dst;
     }
     if (a != f) HIPTRY(hipMemcpyAsync(f, a, bytes, hipMemcpyDeviceToDevice, c->stream));
-    // f may be the context's own buffer
-    if (c->tile || c->pipe) {
-        c->ghosts_stale = reflect;
-        c->recorded |= reflect && is_recording(c->stream);
-    }
+    // the multi-step forms write no ghosts: f leaves with its ring, as after
+    // one-step passes (it may be the context's own buffer, and the copy may
+    // have brought the ring of an f_tmp that never had one)
+    if (ring && (c->tile || c->pipe || a != f))
+        HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, 2 * (c->nx + c->ny), f, 3, c->stream));
     return MRT_OK;
 }
 

@@ -192,3 +192,46 @@ def test_walls_after_fields_that_were_only_recorded():
         got = s.populations()
         assert np.max(np.abs(got - want)) <= 1e-12 * np.abs(want).max()
         s.close()
+
+
+@pytest.mark.parametrize("form,nsteps", [("pipeline", 4), ("tile", 3)])
+def test_ghost_ring_after_a_checkpointed_run_that_ends_in_the_second_buffer(form, nsteps):
+    """One multi-step pass ends in f_tmp, here a buffer of the caller's whose
+    ghost ring was never filled: the copy back into the context's own buffer
+    leaves it with its fixed equilibria, which the pipeline then reads.  A
+    checkpoint has its ring too: the one-step kernel goes on from its bytes."""
+    from ctypes import c_void_p
+
+    from paper_1004_5442_amd import lib as L
+    case = smooth_case(90, 30, ("eq", "eq", "reflect", "reflect"), seed=6)
+    print(f"case {case.name} {form} checkpointed run of one pass", flush=True)
+    s = solver_for_case(case, "fp64")
+    if form == "pipeline":
+        s.set_pipeline(0)
+    cur, _ = s.buffers()
+    tmp, ck = s.empty_state(), [s.empty_state() for _ in range(2)]
+
+    def run(n, segment):
+        ptrs = (c_void_p * 2)(*[t.data_ptr() for t in ck])
+        assert L.raw().mrt_step_checkpointed(s._h, c_void_p(cur), c_void_p(tmp.data_ptr()), segment, n, ptrs) == 0
+
+    def check(n):
+        want, _ = oracle_run(case, n)
+        assert np.max(np.abs(s.populations() - want)) <= 1e-12 * np.abs(want).max(), n
+
+    run(nsteps, nsteps)
+    s.set_pipeline(0)
+    s.step(4)
+    check(nsteps + 4)
+    s.close()
+    s = solver_for_case(case, "fp64")
+    if form == "pipeline":
+        s.set_pipeline(0)
+    cur, _ = s.buffers()
+    run(2 * nsteps, nsteps)
+    s.set_steps_per_pass(1, 0)
+    own = next(b for b in s._bufs if b.data_ptr() == s.buffers()[0])
+    own.copy_(ck[1])
+    s.step(3)
+    check(nsteps + 3)
+    s.close()
