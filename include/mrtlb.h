@@ -168,7 +168,9 @@ int mrt_get_populations(mrt_ctx* ctx, double* f, int on_device);
 int mrt_set_populations(mrt_ctx* ctx, const double* f, int on_device);
 
 /* Raw device pointer of the current population buffer (storage precision,
- * padded layout) and of the other (scratch) buffer. */
+ * padded layout) and of the other (scratch) buffer.  The ghosts of reflecting
+ * walls are brought up to date first where the steps taken left them stale
+ * (one launch on the context's stream). */
 int mrt_current_buffer(mrt_ctx* ctx, void** cur, void** other);
 
 /* Synchronise the stream and test the health flag (MRT_EUNSTABLE if set;

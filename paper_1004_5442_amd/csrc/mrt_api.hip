@@ -1129,6 +1129,13 @@ int mrt_set_populations(mrt_ctx* c, const double* f, int on_device) {
 
 int mrt_current_buffer(mrt_ctx* c, void** cur, void** other) {
     if (!c) return MRT_EINVAL;
+    std::string& ctx_err = c->err;
+    // the caller may copy the state away whole and bring it back later: its
+    // wall ghosts, which the multi-step forms do not write, go with it
+    if (c->ghosts_stale || c->recorded) {
+        HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, 2 * (c->nx + c->ny), c->f[c->cur], 1, c->stream));
+        if (!is_recording(c->stream)) c->ghosts_stale = false;
+    }
     if (cur) *cur = c->f[c->cur];
     if (other) *other = c->f[1 - c->cur];
     return MRT_OK;

@@ -235,3 +235,25 @@ def test_ghost_ring_after_a_checkpointed_run_that_ends_in_the_second_buffer(form
     s.step(3)
     check(nsteps + 3)
     s.close()
+
+
+@pytest.mark.parametrize("form", ["pipeline", "tile"])
+def test_walls_of_a_state_copied_away_and_back(form):
+    """A state's bytes saved after multi-step passes and brought back under
+    the one-step kernel, which reads the wall ghosts among them."""
+    case = smooth_case(90, 30, ("reflect", "reflect", "reflect", "reflect"), seed=8)
+    print(f"case {case.name} {form} state copied away and back", flush=True)
+    s = solver_for_case(case, "fp64")
+    if form == "pipeline":
+        s.set_pipeline(0)
+    s.step(8)
+    cur, _ = s.buffers()
+    own = next(b for b in s._bufs if b.data_ptr() == cur)
+    saved = own.clone()
+    s.set_steps_per_pass(1, 0)
+    s.step(2)
+    own.copy_(saved)
+    s.step(3)
+    want, _ = oracle_run(case, 11)
+    assert np.max(np.abs(s.populations() - want)) <= 1e-12 * np.abs(want).max()
+    s.close()
