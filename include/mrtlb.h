@@ -435,6 +435,22 @@ int mrt_host_cell_adjoint(double gamma, const double* s, double dt, const double
                           const double* lam, double* coll, double* dsk);
 int mrt_host_conserved_fp32(const float* f, float* q);
 
+/* The form in which a context of this grid takes whole passes of mrt_step by
+ * default, before any mrt_set_* or mrt_autotune:
+ *   MRT_FORM_STEPS     one or two steps per pass (rows: the band height)
+ *   MRT_FORM_PIPELINE  the level pipeline (rows: the band height; waves: per
+ *                      level, 2 or 4)
+ *   MRT_FORM_TILE      the tile march (rows of a block)
+ *   MRT_FORM_TUBE      the tube march (waves: per row)
+ * and the steps of a pass.  Any output may be NULL.  MRT_EINVAL where
+ * mrt_init_grid gives it. */
+#define MRT_FORM_STEPS    0
+#define MRT_FORM_PIPELINE 1
+#define MRT_FORM_TILE     2
+#define MRT_FORM_TUBE     3
+int mrt_host_default_form(int nx, int ny, int precision, const int bc[4], int* form, int* steps,
+                          int* rows, int* waves);
+
 #ifdef __cplusplus
 }
 #endif

@@ -382,10 +382,12 @@ PipeShape pipe_shape(int nx, int ny, int prec, int rows) {
         if (waves == 4 && prec == MRT_FP64) break;
         const long long slots = 256 * (prec == MRT_FP64 ? 2 : 4) / waves;
         const long long chunks = (nx + mrt::pipe_width(waves) - 1) / mrt::pipe_width(waves);
-        for (long long rounds = 1; rounds <= 64; ++rounds) {
+        // from the rounds that one band takes (many on grids millions of
+        // columns wide)
+        const long long first = (chunks + slots - 1) / slots;
+        for (long long rounds = first; rounds < first + 64; ++rounds) {
             long long bands = std::min<long long>(ny, slots * rounds / chunks);
             if (rows > 0) bands = (ny + rows - 1) / rows;
-            if (bands < 1) continue;
             const long long r = (ny + bands - 1) / bands;
             const long long n = rows > 0 ? (chunks * bands + slots - 1) / slots : rounds;
             const long long cost = n * (r + kPipeFill);
@@ -448,6 +450,33 @@ Form default_form(int nx, int ny, int prec, const int bc[4], int per_pass, const
     const double piped = pipe.cost * iteration[prec] / kPipeSteps;
     if (tile.us < steps && tile.us < piped) return Form::Tile;
     return piped < steps ? Form::Pipe : Form::Steps;
+}
+
+// Stores bypass the caches (non-temporal) once one population buffer is
+// larger than the 256 MB last-level cache: nothing of the new state can stay
+// cached until the next step anyway.  Smaller grids keep it cached.
+constexpr long long kNonTemporalBytes = 256LL << 20;
+
+// What a grid runs by default when the tube march does not cover it: the
+// steps per pass (1 or 2) of the step kernels, and the form of whole passes.
+struct DefaultForm {
+    int per_pass = 1;
+    Form form = Form::Steps;
+    PipeShape pipe;
+    TileShape tile;
+};
+DefaultForm grid_form(int nx, int ny, int prec, const int bc[4]) {
+    DefaultForm d;
+    // grids larger than the last-level cache (HBM-bound with one step per
+    // pass: 4096^2 FP32 storage 0.65 -> 0.96, FP64 0.68 -> 0.93 of the
+    // per-step roofline with two) and cache-resident ones from about 1024^2
+    // on run two steps per pass by default
+    const bool beyond = elems_for(nx, ny) * (long long)elem_size(prec) > kNonTemporalBytes;
+    d.per_pass = two_step_default(nx, ny, beyond) ? 2 : 1;
+    d.pipe = pipe_shape(nx, ny, prec, 0);
+    d.tile = tile_shape(nx, ny, prec, bc);
+    d.form = default_form(nx, ny, prec, bc, d.per_pass, d.pipe, d.tile);
+    return d;
 }
 
 // Launch shape of the tube march: waves per row (a block holds 64 x waves
@@ -715,11 +744,6 @@ int build_adjoint_items(mrt_ctx* c) {
     return MRT_OK;
 }
 
-// Stores bypass the caches (non-temporal) once one population buffer is
-// larger than the 256 MB last-level cache: nothing of the new state can stay
-// cached until the next step anyway.  Smaller grids keep it cached.
-constexpr long long kNonTemporalBytes = 256LL << 20;
-
 // Grids with reflecting walls up to this many cells have the step kernel
 // write the wall ghosts of its output (one launch per step instead of two:
 // the launch latency dominates there); larger ones refill them with the
@@ -805,30 +829,20 @@ int mrt_init_grid(mrt_ctx** out, int nx, int ny, int precision, const int bc[4],
     c->d_scratch = scratch_address(c->scratch_err);
     c->nt = (long long)bytes > kNonTemporalBytes;
     c->walls = has_kind(bc, MRT_BC_REFLECT) && (long long)nx * ny <= kWallsInKernelCells;
-    // grids larger than the last-level cache (HBM-bound with one step per
-    // pass: 4096^2 FP32 storage 0.65 -> 0.96, FP64 0.68 -> 0.93 of the
-    // per-step roofline with two) and cache-resident ones from about 1024^2
-    // on run two steps per pass by default
-    if (two_step_default(nx, ny, c->nt)) {
-        if (build_items2(c, default_rows2(nx, ny, precision)) != MRT_OK) return fail(MRT_EDEVICE);
-        c->per_pass = 2;
-    }
+    const DefaultForm form = grid_form(nx, ny, precision, bc);
+    c->per_pass = form.per_pass;
+    if (form.per_pass == 2 && build_items2(c, default_rows2(nx, ny, precision)) != MRT_OK) return fail(MRT_EDEVICE);
     // grids the tube march covers (1, 2 or 4 periodic rows, fixed-equilibrium
-    // x sides: the shock tubes) run four steps per pass by default
+    // x sides: the shock tubes) run four steps per pass and more by default
     if (tube_inst_ok(c->inst)) {
         if (build_items4(c) != MRT_OK) return fail(MRT_EDEVICE);
         c->per_pass = kTubeSteps;
-    } else {
-        const PipeShape pipe = pipe_shape(nx, ny, precision, 0);
-        const TileShape tile = tile_shape(nx, ny, precision, bc);
-        const Form form = default_form(nx, ny, precision, bc, c->per_pass, pipe, tile);
-        if (form == Form::Pipe) {
-            if (build_items_pipe(c, pipe) != MRT_OK) return fail(MRT_EDEVICE);
-            c->pipe = true;
-        } else if (form == Form::Tile) {
-            if (build_items_tile(c, tile) != MRT_OK) return fail(MRT_EDEVICE);
-            c->tile = true;
-        }
+    } else if (form.form == Form::Pipe) {
+        if (build_items_pipe(c, form.pipe) != MRT_OK) return fail(MRT_EDEVICE);
+        c->pipe = true;
+    } else if (form.form == Form::Tile) {
+        if (build_items_tile(c, form.tile) != MRT_OK) return fail(MRT_EDEVICE);
+        c->tile = true;
     }
     (void)ctx_err;
     *out = c;
@@ -2271,6 +2285,29 @@ int mrt_host_cell_adjoint(double gamma, const double* s, double dt, const double
     for (int k = 0; k < 16; ++k) sdt[k] = k < 4 ? 0.0 : s[k] * dt;
     const double b = 2.0 / (gamma - 1.0);
     mrt::cell_adjoint<double>(f, lam, b, 1.0 / b, sdt, dt, coll, dsk);
+    return MRT_OK;
+}
+
+int mrt_host_default_form(int nx, int ny, int precision, const int bc[4], int* form, int* steps, int* rows,
+                          int* waves) {
+    if (!size_ok(nx, ny) || precision < 0 || precision > 2 || !bc || !bc_ok(bc)) return MRT_EINVAL;
+    Inst I{};
+    I.ny = ny;
+    for (int k = 0; k < 4; ++k) I.bc[k] = bc[k];
+    const DefaultForm d = grid_form(nx, ny, precision, bc);
+    int out[4] = {MRT_FORM_STEPS, d.per_pass,
+                  d.per_pass == 2 ? default_rows2(nx, ny, precision) : default_rows(nx, ny), 0};
+    if (tube_inst_ok(I)) {
+        const TubeShape t = tube_shape({nx}, ny, precision);
+        out[0] = MRT_FORM_TUBE; out[1] = t.steps; out[2] = ny; out[3] = t.waves;
+    } else if (d.form == Form::Pipe) {
+        out[0] = MRT_FORM_PIPELINE; out[1] = kPipeSteps; out[2] = d.pipe.rows; out[3] = d.pipe.waves;
+    } else if (d.form == Form::Tile) {
+        out[0] = MRT_FORM_TILE; out[1] = d.tile.steps; out[2] = d.tile.rows;
+    }
+    int* to[4] = {form, steps, rows, waves};
+    for (int k = 0; k < 4; ++k)
+        if (to[k]) *to[k] = out[k];
     return MRT_OK;
 }
 

@@ -22,6 +22,7 @@ MRT_OK, MRT_EINVAL, MRT_EDEVICE, MRT_ESTATE, MRT_EUNSTABLE, MRT_ENOMEM = 0, -1, 
 PRECISION = {"fp64": 0, "fp32": 1, "fp32_eq64": 2}
 BC = {"periodic": 0, "eq": 1, "outflow": 2, "reflect": 3}
 SCHEME_SPLIT, SCHEME_LW_CROSS = 1, 2
+FORM = ("steps", "pipeline", "tile", "tube")
 STATUS = {0: "MRT_OK", -1: "MRT_EINVAL", -2: "MRT_EDEVICE", -3: "MRT_ESTATE",
           -4: "MRT_EUNSTABLE", -5: "MRT_ENOMEM"}
 
@@ -104,6 +105,7 @@ _proto = {
     "mrt_host_collision": (c_int, [c_double, _D, c_double, _D, _D]),
     "mrt_host_cell_adjoint": (c_int, [c_double, _D, c_double, _D, _D, _D, _D]),
     "mrt_host_conserved_fp32": (c_int, [_F, _F]),
+    "mrt_host_default_form": (c_int, [c_int, c_int, c_int, POINTER(c_int)] + [POINTER(c_int)] * 4),
 }
 for _name, (_res, _args) in _proto.items():
     _fn = getattr(_lib, _name)
@@ -185,3 +187,12 @@ def host_conserved_fp32(f):
     q = np.empty(4, dtype=np.float32)
     check(_lib.mrt_host_conserved_fp32(f.ctypes.data_as(_F), q.ctypes.data_as(_F)))
     return q
+
+
+def host_default_form(nx, ny, precision="fp32_eq64", bc=("periodic",) * 4):
+    """(form, steps of a pass, rows, waves) that a grid runs by default
+    (mrt_host_default_form; form: one of FORM)."""
+    out = [c_int() for _ in range(4)]
+    check(_lib.mrt_host_default_form(int(nx), int(ny), PRECISION[precision], (c_int * 4)(*[BC[b] for b in bc]),
+                                     *[byref(v) for v in out]))
+    return (FORM[out[0].value],) + tuple(v.value for v in out[1:])

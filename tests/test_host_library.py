@@ -138,3 +138,32 @@ def test_fp32_conserved_sums_are_correctly_rounded():
     print("correctly rounded:", hits, "of", total, "; plain FP32 sums:", plain_hits)
     assert hits >= 0.999 * total
     assert plain_hits < 0.9 * total
+
+
+@pytest.mark.parametrize("precision,width", [("fp64", 64 * 256 * 120), ("fp32", 64 * 256 * 248),
+                                             ("fp32_eq64", 64 * 256 * 248)])
+def test_default_form_of_grids_millions_of_columns_wide(precision, width):
+    """One band of such a grid takes more than 64 rounds of resident blocks:
+    the launch rule still finds the pipeline's shape (bands of the whole
+    height: more of them would only repeat the fill), on either side of that
+    width, and prefers it only where its expected time is the shortest."""
+    for ny in (1, 3, 8, 20, 50):
+        below, above = (lib.host_default_form(int(width * k), ny, precision) for k in (0.98, 1.02))
+        assert below == above, (ny, below, above)
+        form, steps, rows, _ = above
+        if form == "pipeline":
+            assert rows == ny, above
+    assert lib.host_default_form(2_000_000, 1, precision)[0] == "steps"
+    # and the forms known from narrower grids are as they were
+    assert lib.host_default_form(4096, 4096, "fp32_eq64", ("outflow",) * 4) == ("pipeline", 4, 274, 4)
+    assert lib.host_default_form(1024, 1024, "fp64", ("outflow",) * 4) == ("pipeline", 4, 37, 2)
+    assert lib.host_default_form(128, 96) == ("tile", 3, 8, 0)
+    assert lib.host_default_form(400, 4, "fp64", ("eq", "eq", "periodic", "periodic"))[0] == "tube"
+
+
+def test_default_form_rejects_what_a_context_rejects():
+    for args in ((0, 5), (5, 0), (20000, 20000)):
+        with pytest.raises(lib.MRTError):
+            lib.host_default_form(*args)
+    with pytest.raises(lib.MRTError):
+        lib.host_default_form(64, 64, "fp64", ("periodic", "eq", "periodic", "periodic"))
