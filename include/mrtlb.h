@@ -237,6 +237,32 @@ int mrt_get_steps_per_pass(const mrt_ctx* ctx, int* steps, int* rows);
 int mrt_set_pipeline(mrt_ctx* ctx, int rows);
 int mrt_get_pipeline(const mrt_ctx* ctx, int* rows);
 
+/* The tile march: several time steps per kernel launch for small grids of
+ * any boundary kinds, in every precision (default scheme only).  A block
+ * holds `rows` rows of 64 columns, advances them `steps` steps and stores the
+ * cells that are exact (the overlap of `steps` cells on every side is
+ * recomputed by the neighbouring blocks).  Steps left over take one shorter
+ * launch.  Results equal single steps to rounding order (bit-identical in
+ * pure FP32), and do not depend on how a number of steps is split over calls.
+ * rows: 8, 12 or, in FP32 storage, 16 (0: by grid size), -1 turns it off;
+ * steps: 1 to 6, fewer than half the rows (0: by grid size).  mrt_init_grid
+ * turns it on for small grids.  Turning it on or off also ends the level
+ * pipeline.  Errors: MRT_EINVAL. */
+int mrt_set_tile_march(mrt_ctx* ctx, int rows, int steps);
+
+/* The form in which mrt_step takes whole passes, and the steps of one:
+ *   MRT_FORM_STEPS     one or two steps per pass (rows: the band height)
+ *   MRT_FORM_PIPELINE  the level pipeline (rows: the band height; waves: per
+ *                      level, 2 or 4)
+ *   MRT_FORM_TILE      the tile march (rows of a block)
+ *   MRT_FORM_TUBE      the tube march (waves: per row)
+ * Any output may be NULL. */
+#define MRT_FORM_STEPS    0
+#define MRT_FORM_PIPELINE 1
+#define MRT_FORM_TILE     2
+#define MRT_FORM_TUBE     3
+int mrt_get_form(const mrt_ctx* ctx, int* form, int* steps, int* rows, int* waves);
+
 /* Scheme variants (the paper's discretisation passage admits three
  * readings; section "Construction", last paragraph before Fig. 1):
  *   0                      unsplit forward Euler, per-axis Lax-Wendroff
@@ -435,19 +461,9 @@ int mrt_host_cell_adjoint(double gamma, const double* s, double dt, const double
                           const double* lam, double* coll, double* dsk);
 int mrt_host_conserved_fp32(const float* f, float* q);
 
-/* The form in which a context of this grid takes whole passes of mrt_step by
- * default, before any mrt_set_* or mrt_autotune:
- *   MRT_FORM_STEPS     one or two steps per pass (rows: the band height)
- *   MRT_FORM_PIPELINE  the level pipeline (rows: the band height; waves: per
- *                      level, 2 or 4)
- *   MRT_FORM_TILE      the tile march (rows of a block)
- *   MRT_FORM_TUBE      the tube march (waves: per row)
- * and the steps of a pass.  Any output may be NULL.  MRT_EINVAL where
- * mrt_init_grid gives it. */
-#define MRT_FORM_STEPS    0
-#define MRT_FORM_PIPELINE 1
-#define MRT_FORM_TILE     2
-#define MRT_FORM_TUBE     3
+/* The form (see mrt_get_form) in which a context of this grid takes whole
+ * passes of mrt_step by default, before any mrt_set_* or mrt_autotune.  Any
+ * output may be NULL.  MRT_EINVAL where mrt_init_grid gives it. */
 int mrt_host_default_form(int nx, int ny, int precision, const int bc[4], int* form, int* steps,
                           int* rows, int* waves);
 

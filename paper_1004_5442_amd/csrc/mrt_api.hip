@@ -412,13 +412,15 @@ struct TileShape {
     int rows = 8, steps = 1;
     double us = -1;
 };
-TileShape tile_shape(int nx, int ny, int prec, const int bc[4]) {
+// `only_rows`, `only_steps`: 0, or the shape's rows or steps are given.
+TileShape tile_shape(int nx, int ny, int prec, const int bc[4], int only_rows = 0, int only_steps = 0) {
     const bool fp64 = prec == MRT_FP64, walls = has_kind(bc, MRT_BC_REFLECT);
     const double start = 4.0, chain = 1.4, wave = fp64 ? 1.0 : 0.69, wall = walls ? 0.9 : 0.0;
     const int most = fp64 ? 12 : 16;
     TileShape best;
     for (int rows = 8; rows <= most; rows += 4)
-        for (int steps = 2; steps <= mrt::kTileMaxSteps && 2 * steps < rows; ++steps) {
+        for (int steps = only_steps == 1 ? 1 : 2; steps <= mrt::kTileMaxSteps && 2 * steps < rows; ++steps) {
+            if ((only_rows && rows != only_rows) || (only_steps && steps != only_steps)) continue;
             const int w = mrt::tile_width(steps), h = mrt::tile_height(rows, steps);
             const double blocks = double((nx + w - 1) / w) * ((ny + h - 1) / h);
             const double rounds = std::ceil(blocks / 256.0);
@@ -1224,6 +1226,44 @@ int mrt_set_pipeline(mrt_ctx* c, int rows) {
 int mrt_get_pipeline(const mrt_ctx* c, int* rows) {
     if (!c) return MRT_EINVAL;
     if (rows) *rows = c->pipe ? c->rows_p : -1;
+    return MRT_OK;
+}
+
+int mrt_set_tile_march(mrt_ctx* c, int rows, int steps) {
+    if (!c) return MRT_EINVAL;
+    if (rows >= 0) {
+        const TileShape shape = rows == 0 || rows == 8 || rows == 12 || (rows == 16 && c->prec != MRT_FP64)
+                                    ? tile_shape(c->nx, c->ny, c->prec, c->bc, rows, steps)
+                                    : TileShape{};
+        if (shape.us < 0)
+            return ctx_fail(c, MRT_EINVAL, "rows: -1 (off), 0 (default), 8, 12 or, in FP32 storage, 16; "
+                                           "steps: 0 (default) or 1 to 6, fewer than half the rows");
+        if (shape.rows != c->tile_form.rows || shape.steps != c->tile_form.steps || !c->d_items_t) {
+            const int rc = build_items_tile(c, shape);
+            if (rc != MRT_OK) return rc;
+        }
+    } else if (rows < -1) {
+        return ctx_fail(c, MRT_EINVAL, "rows: -1 (off), 0 (default), 8, 12 or 16");
+    }
+    c->tile = rows >= 0;
+    c->pipe = false;
+    return MRT_OK;
+}
+
+int mrt_get_form(const mrt_ctx* c, int* form, int* steps, int* rows, int* waves) {
+    if (!c) return MRT_EINVAL;
+    int out[4] = {MRT_FORM_STEPS, c->scheme ? 1 : c->per_pass,
+                  !c->scheme && c->per_pass == 2 ? c->rows2 : c->rows, 0};
+    if (c->scheme == 0 && c->pipe) {
+        out[0] = MRT_FORM_PIPELINE; out[1] = kPipeSteps; out[2] = c->rows_p; out[3] = c->waves_p;
+    } else if (c->scheme == 0 && c->tile) {
+        out[0] = MRT_FORM_TILE; out[1] = c->tile_form.steps; out[2] = c->tile_form.rows;
+    } else if (c->scheme == 0 && c->per_pass == kTubeSteps) {
+        out[0] = MRT_FORM_TUBE; out[1] = c->tube.steps; out[2] = c->ny; out[3] = c->tube.waves;
+    }
+    int* to[4] = {form, steps, rows, waves};
+    for (int k = 0; k < 4; ++k)
+        if (to[k]) *to[k] = out[k];
     return MRT_OK;
 }
 

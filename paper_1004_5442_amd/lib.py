@@ -73,6 +73,8 @@ _proto = {
     "mrt_get_steps_per_pass": (c_int, [c_void_p, POINTER(c_int), POINTER(c_int)]),
     "mrt_set_pipeline": (c_int, [c_void_p, c_int]),
     "mrt_get_pipeline": (c_int, [c_void_p, POINTER(c_int)]),
+    "mrt_set_tile_march": (c_int, [c_void_p, c_int, c_int]),
+    "mrt_get_form": (c_int, [c_void_p] + [POINTER(c_int)] * 4),
     "mrt_autotune": (c_int, [c_void_p, c_int]),
     "mrt_destroy": (None, [c_void_p]),
     "mrt_last_error": (ctypes.c_char_p, [c_void_p]),

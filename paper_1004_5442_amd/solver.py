@@ -184,6 +184,18 @@ class Solver:
         self._check(L.raw().mrt_get_pipeline(self._h, byref(r)))
         return r.value
 
+    def set_tile_march(self, rows: int = 0, steps: int = 0):
+        """Several steps at a time by the tile march (mrt_set_tile_march);
+        rows of a block (0: default, -1: off) and steps of a pass."""
+        self._check(L.raw().mrt_set_tile_march(self._h, int(rows), int(steps)))
+
+    def form(self):
+        """(form, steps of a pass, rows, waves) of whole passes
+        (mrt_get_form; form: one of lib.FORM)."""
+        out = [c_int() for _ in range(4)]
+        self._check(L.raw().mrt_get_form(self._h, *[byref(v) for v in out]))
+        return (L.FORM[out[0].value],) + tuple(v.value for v in out[1:])
+
     def set_tile(self, rows: int, grid: int = 0):
         self._check(L.raw().mrt_set_tile(self._h, int(rows), int(grid)))
 

@@ -443,3 +443,39 @@ def test_riemann2d_1024_stated_tolerance(precision):
     err = _riemann2d_2000()[precision]
     print(precision, "stated-tolerance check", err, flush=True)
     assert all(v < 1e-5 for v in err.values()), (precision, err)
+
+
+@pytest.mark.parametrize("precision", ["fp32_eq64", "fp32", "fp64"])
+def test_shock_bubble_4096_in_the_default_form(precision):
+    """The large shock-bubble grid as a context runs it by default, the level
+    pipeline (four waves per level in FP32 storage): two whole passes and two
+    steps left over, sampled, the bubble edge also on the blocks' seams."""
+    n, nsteps = 4096, 10
+    case = W.shock_bubble(n=n)
+    s = solver_for_case(case, precision)
+    print(f"case {case.name} {precision} default form {s.form()}", flush=True)
+    assert s.form()[0] == "pipeline" and s.form()[3] == (2 if precision == "fp64" else 4)
+    s.step(nsteps)
+    s.sync()
+    width = 120 if precision == "fp64" else 248
+    bx, by, br = int(0.25 * n), n // 2, int(0.1 * n)
+    seams = [k * width for k in range(n // width) if abs(k * width - bx) < br]
+    centres = shock_bubble_centres(n) + [(x, by + int(np.sqrt(br * br - (bx - x) ** 2))) for x in seams[:3]]
+    compare(case, s, centres, nsteps, precision)
+    s.close()
+
+
+def test_two_step_kernel_past_the_signed_32_bit_offset_range():
+    """12000 x 12000 cells, FP32 storage, by the two-step kernel."""
+    n = 12000
+    case = W.shock_bubble(n=n)
+    print(f"case {case.name} fp32_eq64 {NSTEPS} steps, two per pass", flush=True)
+    s = solver_for_case(case, "fp32_eq64")
+    s.set_steps_per_pass(2, 0)
+    assert s.form()[:2] == ("steps", 2)
+    s.step(NSTEPS)
+    s.sync()
+    centres = [(int(0.1 * n), n // 2), (int(0.1 * n), 0), (int(0.15 * n), n // 2),
+               (n // 2, n - 1), (0, 0), (n - 1, n - 1), (n - 1, 0), (0, n - 1)]
+    compare(case, s, centres, NSTEPS, "fp32_eq64")
+    s.close()

@@ -257,3 +257,27 @@ def test_walls_of_a_state_copied_away_and_back(form):
     want, _ = oracle_run(case, 11)
     assert np.max(np.abs(s.populations() - want)) <= 1e-12 * np.abs(want).max()
     s.close()
+
+
+# band heights and shapes that the launch rule gives four waves per level (248 stored columns):
+# around one and two such blocks, a last block of 234 and of one column, the width of the headline grid
+WIDE = [((248, 180), 1), ((241, 175), 1), ((496, 110), 1), ((730, 80), 1), ((14881, 62), 1), ((4096, 60), 4)]
+
+
+@pytest.mark.parametrize("prec", ["fp32_eq64", "fp32"])
+@pytest.mark.parametrize("bc", BC_SETS)
+@pytest.mark.parametrize("shape,rows", WIDE)
+def test_four_waves_per_level_match_single_steps(shape, rows, bc, prec):
+    case = smooth_case(*shape, bc, seed=sum(shape), dt=2e-5 if max(shape) < 5000 else 5e-6)
+    print(f"case {case.name} bc={bc} {prec} four waves per level", flush=True)
+    one, pipe = solver_for_case(case, prec), solver_for_case(case, prec)
+    one.set_steps_per_pass(1, 0)
+    pipe.set_pipeline(rows)
+    assert pipe.form() == ("pipeline", 4, rows, 4)
+    for s in (one, pipe):
+        s.step(8)
+    a, b = pipe.populations(), one.populations()
+    d = float(np.max(np.abs(a - b)) / np.abs(b).max())
+    assert d <= (0.0 if prec == "fp32" else 1e-6), d
+    one.close()
+    pipe.close()

@@ -62,3 +62,87 @@ def test_tile_march_matches_oracle_and_single_steps(shape, bc, prec):
         assert max(err.values()) < 1e-5, err
     for s in (one, tile, again):
         s.close()
+
+
+# (rows of a block, steps of a launch): every row count, the smallest, largest and middle overlaps
+FORMS = [(8, 1), (8, 2), (8, 3), (12, 2), (12, 4), (12, 5), (16, 2), (16, 3), (16, 4), (16, 6)]
+TOLERANCE = {"fp64": 1e-13, "fp32_eq64": 2.4e-7, "fp32": 0.0}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_eq64", "fp32"])
+@pytest.mark.parametrize("bc", BC_SETS)
+@pytest.mark.parametrize("rows,steps", FORMS)
+def test_every_launch_shape_matches_oracle_and_single_steps(rows, steps, bc, prec):
+    """Each kernel of the march by name, with and without walls: grids that
+    end inside a tile, one cell into the next, and smaller than the overlap."""
+    if prec == "fp64" and rows == 16:
+        s = solver_for_case(smooth_case(57, 9, bc, seed=1), prec)
+        with pytest.raises(RuntimeError, match="rows"):
+            s.set_tile_march(rows, steps)
+        s.close()
+        return
+    width, height, nsteps = 64 - 2 * steps, rows - 2 * steps, 13
+    for nx, ny in ((width + 1, 2 * height + 1), (2 * width - 1, height), (3, 40), (2, 1)):
+        case = smooth_case(nx, ny, bc, seed=nx + 7 * ny)
+        print(f"case {case.name} bc={bc} {prec} tile march {rows} rows {steps} steps", flush=True)
+        want, p = oracle_run(case, nsteps)
+        one = solver_for_case(case, prec)
+        one.set_steps_per_pass(1, 0)
+        one.step(nsteps)
+        tile = solver_for_case(case, prec)
+        tile.set_tile_march(rows, steps)
+        assert tile.form()[:3] == ("tile", steps, rows)
+        tile.step(nsteps)
+        got, ref, scale = tile.populations(), one.populations(), np.abs(want).max()
+        d = float(np.max(np.abs(got - ref)) / scale)
+        assert d <= TOLERANCE[prec], (nx, ny, d)
+        if prec == "fp64":
+            assert float(np.max(np.abs(got - want)) / scale) <= 1e-12, (nx, ny)
+        else:
+            err = field_errors(tile.moments(), mrt.macroscopic(want, p.b))
+            assert max(err.values()) < 1e-5, (nx, ny, err)
+        one.close()
+        tile.close()
+
+
+@pytest.mark.parametrize("bc", BC_SETS[:3])
+@pytest.mark.parametrize("prec,shape", [("fp64", (256, 256)), ("fp32_eq64", (256, 251)), ("fp32_eq64", (301, 303)),
+                                        ("fp32", (350, 347))])
+def test_default_forms_over_many_blocks_match_single_steps(prec, shape, bc):
+    """The launches that mid-sized grids get by default (12 and 16 rows, and
+    more blocks than CUs) against the one-step kernel."""
+    case = smooth_case(*shape, bc, seed=shape[1])
+    tile, one = solver_for_case(case, prec), solver_for_case(case, prec)
+    print(f"case {case.name} bc={bc} {prec} default form {tile.form()}", flush=True)
+    assert tile.form()[0] == "tile" and tile.form()[2] >= 12
+    one.set_steps_per_pass(1, 0)
+    for s in (tile, one):
+        s.step(13)
+    a, b = tile.populations(), one.populations()
+    assert float(np.max(np.abs(a - b)) / np.abs(b).max()) <= TOLERANCE[prec]
+    tile.close()
+    one.close()
+
+
+def test_forms_are_set_and_told():
+    """mrt_set_tile_march and mrt_get_form: the default form comes back after
+    another one, and what the march does not take is refused."""
+    case = smooth_case(128, 96, BC_SETS[1], seed=3)
+    s = solver_for_case(case, "fp32_eq64")
+    default = s.form()
+    assert default[0] == "tile"
+    s.set_steps_per_pass(2, 8)
+    assert s.form() == ("steps", 2, 8, 0)
+    s.set_pipeline(16)
+    assert s.form()[:3] == ("pipeline", 4, 16)
+    s.set_tile_march()
+    assert s.form() == default and s.pipeline() == -1
+    for rows, steps in ((-2, 0), (4, 0), (20, 0), (8, 4), (12, 6), (16, 7), (8, -1)):
+        with pytest.raises(RuntimeError, match="rows"):
+            s.set_tile_march(rows, steps)
+    assert s.form() == default
+    s.set_tile_march(-1)
+    assert s.form()[0] == "steps"
+    s.set_scheme(split=True)
+    assert s.form()[:2] == ("steps", 1)
+    s.close()
