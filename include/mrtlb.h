@@ -180,7 +180,9 @@ int mrt_sync(mrt_ctx* ctx);
 /* Tile shape of the one-step kernel: rows per work item (>= 1; each work item
  * is 256 columns, one 4-wave workgroup) and workgroups launched (0 = one per
  * work item).  mrt_init_grid picks rows from the grid size (about 8192 work
- * items, at most 6 rows); mrt_autotune replaces them with measured ones. */
+ * items, at most 6 rows); mrt_autotune replaces them with measured ones.
+ * Setting the tile ends the level pipeline and the tile march, which would run
+ * in the step kernels' place; the steps per pass stay as they are. */
 int mrt_set_tile(mrt_ctx* ctx, int rows_per_item, int grid_blocks);
 int mrt_get_tile(const mrt_ctx* ctx, int* rows_per_item, int* grid_blocks);
 
@@ -231,7 +233,8 @@ int mrt_get_steps_per_pass(const mrt_ctx* ctx, int* steps, int* rows);
  * march and than one or two steps per pass (from about 400 x 300 cells on in
  * FP64, 600^2 in FP32 storage; not on the tube march's grids); mrt_autotune
  * times them all, and mrt_set_steps_per_pass, which names another form, turns
- * it off.  Turning it on or off also ends the tile march.
+ * it off, as does mrt_set_tile.  Turning it on or off also ends the tile
+ * march.
  * mrt_get_pipeline gives the band height, -1 when off.  Errors: MRT_EINVAL
  * (rows < -1). */
 int mrt_set_pipeline(mrt_ctx* ctx, int rows);

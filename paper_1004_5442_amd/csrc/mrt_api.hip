@@ -1168,6 +1168,8 @@ int mrt_set_tile(mrt_ctx* c, int rows, int grid) {
     const int rc = build_items(c, std::min(rows, c->ny));
     if (rc != MRT_OK) return rc;
     c->grid = grid;
+    // the forms that run in the step kernels' place would ignore the tile
+    c->pipe = c->tile = false;
     return MRT_OK;
 }
 

@@ -146,3 +146,24 @@ def test_forms_are_set_and_told():
     s.set_scheme(split=True)
     assert s.form()[:2] == ("steps", 1)
     s.close()
+
+
+@pytest.mark.parametrize("shape,form", [((300, 40), "tile"), ((800, 800), "pipeline")])
+def test_setting_the_tile_names_the_step_kernels(shape, form):
+    """mrt_set_tile shapes the one-step kernel, so that kernel runs then, not
+    the form that the grid has by default."""
+    case = smooth_case(*shape, BC_SETS[1], seed=12)
+    print(f"case {case.name} default {form}, then a tile", flush=True)
+    a, b = solver_for_case(case, "fp64"), solver_for_case(case, "fp64")
+    assert a.form()[0] == form
+    a.step(8)
+    b.set_steps_per_pass(1, 0)
+    b.set_populations(a.populations())
+    for s in (a, b):
+        s.set_tile(3)
+    assert a.form() == ("steps", 1, 3, 0) and a.pipeline() == -1 and a.tile() == (3, 0)
+    for s in (a, b):
+        s.step(5)
+    assert np.array_equal(a.populations(), b.populations())
+    a.close()
+    b.close()
