@@ -1426,12 +1426,12 @@ struct PipeRows {
 };
 
 // One dword per lane from global memory (a + off) to LDS (lds + 4 lane),
-// without passing through registers; the caller waits with dma_wait().  (M0,
-// which the compiler sets itself before each of its own uses, holds the LDS
-// address.)
+// without passing through registers; the caller waits with dma_wait().  M0
+// holds the LDS address and is declared clobbered: the compiler may keep a
+// value of its own there.
 __device__ __forceinline__ void dma_dword(unsigned long long a, unsigned off, unsigned lds) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, %0"
-                 :: "s"(a), "v"(off), "s"(lds) : "memory");
+                 :: "s"(a), "v"(off), "s"(lds) : "memory", "m0");
 }
 // Waits until at most N of this wave's memory operations are in flight.
 template <int N>

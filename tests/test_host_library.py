@@ -167,3 +167,14 @@ def test_default_form_rejects_what_a_context_rejects():
             lib.host_default_form(*args)
     with pytest.raises(lib.MRTError):
         lib.host_default_form(64, 64, "fp64", ("periodic", "eq", "periodic", "periodic"))
+
+
+def test_inline_assembly_declares_the_registers_it_writes():
+    """Every inline asm statement of the kernels that writes M0 by name lists
+    it as clobbered (no operand stands for it)."""
+    src = open(os.path.join(ROOT, "paper_1004_5442_amd", "csrc", "mrt_kernels.hip")).read()
+    asms = re.findall(r"asm volatile\((.*?)\);", src, flags=re.S)
+    writes = [a for a in asms if re.search(r"\bs_mov_b32 m0\b", a)]
+    assert writes
+    for a in writes:
+        assert '"m0"' in a.rsplit(":", 1)[1], a
