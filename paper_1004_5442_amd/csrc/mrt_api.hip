@@ -450,7 +450,13 @@ Form default_form(int nx, int ny, int prec, const int bc[4], int per_pass, const
     const double walls = has_kind(bc, MRT_BC_REFLECT) ? 1.5 : 0.0;
     const double steps = per_pass == 2 ? cells / rate2[prec] : std::max(4.3, 2.2 + cells / rate1[prec]) + walls;
     const double piped = pipe.cost * iteration[prec] / kPipeSteps;
-    if (tile.us < steps && tile.us < piped) return Form::Tile;
+    // The tile march's time has no term for memory, and its blocks read the
+    // overlaps again: where one step per pass is no longer the rule the
+    // pipeline, which reads each row once, runs in its place (FP64, us per step
+    // of the march, two steps per pass and the pipeline: 2,000,000 x 8 710, 644,
+    // 443; 100,000 x 16 77, 74, 43; 131,072 x 8 45, 39, 34; 56 x 30,000 79, 238,
+    // 60; no FP32 grid comes here).
+    if (tile.us < steps && tile.us < piped) return per_pass == 1 ? Form::Tile : Form::Pipe;
     return piped < steps ? Form::Pipe : Form::Steps;
 }
 

@@ -178,3 +178,14 @@ def test_inline_assembly_declares_the_registers_it_writes():
     assert writes
     for a in writes:
         assert '"m0"' in a.rsplit(":", 1)[1], a
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_eq64"])
+def test_the_tile_march_is_left_to_grids_of_one_step_per_pass(precision):
+    """Where two steps per pass would run (512 bands of 8 rows x 256 columns)
+    the state's way through memory counts, which the tile march repeats."""
+    for nx, ny in ((2_000_000, 8), (1_000_000, 8), (100_000, 16), (131_072, 8), (65_536, 16), (40_000, 32),
+                   (1024, 1024), (8, 5000), (40, 4096), (256, 4096)):
+        assert -(-nx // 256) * -(-ny // 8) >= 512
+        assert lib.host_default_form(nx, ny, precision)[0] != "tile", (nx, ny)
+    assert lib.host_default_form(100_000, 8, precision)[0] == "tile"
