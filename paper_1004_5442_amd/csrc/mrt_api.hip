@@ -577,6 +577,8 @@ struct mrt_ctx {
     TileShape tile_form;
     Item* d_items_t = nullptr;       // its work items
     int nitems_t = 0;
+    Item* d_items_t1 = nullptr;      // and those of a launch of one step (kTileOneRows rows)
+    int nitems_t1 = 0;
     GraphCache graphs_t;             // captured tile-march passes
     bool ghosts_stale = false;       // reflecting-wall ghosts of the current state (the pipeline and the tile march write none)
     bool recorded = false;           // passes of those forms are in a graph of the caller's: its replays leave them stale unseen
@@ -713,20 +715,45 @@ int build_items_pipe(mrt_ctx* c, const PipeShape& shape) {
     return MRT_OK;
 }
 
+// A launch of one step (steps of a pass left over, or a program that steps one
+// at a time) by a form of more rows takes blocks of 8 rows and an overlap of
+// one instead: the same code for every cell, so the same bits, without the
+// overlap of several steps.  Measured, us per call of one step, the form's own
+// blocks -> these, and the one-step kernel: 4000 x 40 FP32 storage with FP64
+// collision 11.8 -> 7.5 (7.5), with walls 13.8 -> 8.9 (8.5); 500^2 11.6 -> 9.7
+// (9.5); 256^2 FP64 7.6 -> 6.9 (6.3).  (A form of 8 rows gains nothing: 128 x
+// 96 in FP64 5.6 -> 5.9.)
+constexpr int kTileOneRows = 8;
+
 int build_items_tile(mrt_ctx* c, const TileShape& shape) {
     std::string& ctx_err = c->err;
-    const int w = mrt::tile_width(shape.steps), h = mrt::tile_height(shape.rows, shape.steps);
-    std::vector<Item> items;
-    for (int y = 0; y < c->ny; y += h)
-        for (int x = 0; x < c->nx; x += w) items.push_back(Item{0, x, y, std::min(c->ny, y + h)});
-    if (c->d_items_t) HIPTRY(hipFree(c->d_items_t));
-    c->d_items_t = nullptr;
-    HIPTRY(hipMalloc(&c->d_items_t, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(c->d_items_t, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    c->nitems_t = int(items.size());
+    auto table = [&](int rows, int overlap, Item** d, int* n) -> hipError_t {
+        const int w = mrt::tile_width(overlap), h = mrt::tile_height(rows, overlap);
+        std::vector<Item> items;
+        for (int y = 0; y < c->ny; y += h)
+            for (int x = 0; x < c->nx; x += w) items.push_back(Item{0, x, y, std::min(c->ny, y + h)});
+        if (*d) (void)hipFree(*d);
+        *d = nullptr;
+        const hipError_t e = hipMalloc(d, items.size() * sizeof(Item));
+        if (e != hipSuccess) return e;
+        *n = int(items.size());
+        return hipMemcpy(*d, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice);
+    };
+    HIPTRY(table(shape.rows, shape.steps, &c->d_items_t, &c->nitems_t));
+    if (!c->d_items_t1) HIPTRY(table(kTileOneRows, 1, &c->d_items_t1, &c->nitems_t1));
     c->tile_form = shape;
     c->graphs_t.clear();
     return MRT_OK;
+}
+
+// `steps` <= tile_form.steps steps of the tile march (k_tile's buffers).
+hipError_t tile_pass(const mrt_ctx* c, int steps, const void* fin, void* fout, void* const* fouts, hipStream_t st) {
+    const bool walls = has_kind(c->bc, MRT_BC_REFLECT);
+    if (steps == 1 && c->tile_form.rows > kTileOneRows)
+        return mrt::k_tile(c->prec, c->d_inst, c->d_items_t1, c->nitems_t1, kTileOneRows, 1, 1, walls, fin, fout,
+                           fouts, c->d_health, st);
+    return mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows, c->tile_form.steps, steps,
+                       walls, fin, fout, fouts, c->d_health, st);
 }
 
 // Work items of the adjoint kernel: 256-column chunks of row bands, marched
@@ -957,9 +984,7 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
         // remaining steps.  Every step runs the same code however the passes
         // are cut, so that n steps at once and one at a time agree bit for bit
         auto march = [&](int cur, hipStream_t st, int steps) -> hipError_t {
-            return mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
-                               c->tile_form.steps, steps, reflect, c->f[cur], c->f[1 - cur], nullptr, c->d_health,
-                               st);
+            return tile_pass(c, steps, c->f[cur], c->f[1 - cur], nullptr, st);
         };
         auto enqueue_t = [&](int cur, hipStream_t st) -> hipError_t { return march(cur, st, c->tile_form.steps); };
         const int passes = n / c->tile_form.steps, rest = n % c->tile_form.steps;
@@ -1489,6 +1514,7 @@ void mrt_destroy(mrt_ctx* c) {
     if (c->d_items4) (void)hipFree(c->d_items4);
     if (c->d_items_p) (void)hipFree(c->d_items_p);
     if (c->d_items_t) (void)hipFree(c->d_items_t);
+    if (c->d_items_t1) (void)hipFree(c->d_items_t1);
     if (c->f_tmp) (void)hipFree(c->f_tmp);
     c->graphs.clear();
     c->graphs2.clear();
@@ -1590,8 +1616,7 @@ int mrt_step_checkpointed(mrt_ctx* c, void* f, void* f_tmp, int segment, int nst
             // the tile march reads no ghosts, but a checkpoint keeps its ring
             if (ring && a != f && a != f_tmp)
                 HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, 2 * (c->nx + c->ny), a, 3, c->stream));
-            HIPTRY(mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
-                               c->tile_form.steps, m, reflect, a, dst, nullptr, c->d_health, c->stream));
+            HIPTRY(tile_pass(c, m, a, dst, nullptr, c->stream));
         } else if (m == kPipeSteps) {
             if (ring) HIPTRY(mrt::k_ghost(c->prec, c->d_inst, 1, 2 * (c->nx + c->ny), a, 3, c->stream));
             HIPTRY(mrt::k_pipe(c->prec, c->waves_p, c->d_inst, c->d_items_p, c->nitems_p, a, dst, c->d_health,
@@ -1667,9 +1692,7 @@ int mrt_adjoint_sweep(mrt_ctx* c, const void* const* checkpoints, int segment, i
                 const int m = std::min(stop - start - j, c->tile_form.steps);
                 void* outs[mrt::kTileMaxSteps];
                 for (int k = 0; k < m; ++k) outs[k] = const_cast<void*>(state(seg, j + k));
-                const hipError_t e = mrt::k_tile(c->prec, c->d_inst, c->d_items_t, c->nitems_t, c->tile_form.rows,
-                                                 c->tile_form.steps, m, false, state(seg, j - 1), nullptr, outs,
-                                                 c->d_health, st);
+                const hipError_t e = tile_pass(c, m, state(seg, j - 1), nullptr, outs, st);
                 if (e != hipSuccess) return e;
                 j += m;
             }

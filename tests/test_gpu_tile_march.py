@@ -167,3 +167,32 @@ def test_setting_the_tile_names_the_step_kernels(shape, form):
     assert np.array_equal(a.populations(), b.populations())
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_eq64", "fp32"])
+@pytest.mark.parametrize("bc", BC_SETS[:3])
+@pytest.mark.parametrize("rows,steps", [(12, 3), (16, 4)])
+def test_steps_one_at_a_time_equal_a_whole_run(rows, steps, bc, prec):
+    """A launch of one step takes smaller blocks: bit for bit the steps of the
+    whole passes, by whichever blocks, in mrt_step and between buffers."""
+    if prec == "fp64" and rows == 16:
+        rows, steps = 12, 5
+    for nx, ny in ((62, 6), (63, 7), (130, 70), (5, 40)):
+        case = smooth_case(nx, ny, bc, seed=nx)
+        print(f"case {case.name} bc={bc} {prec} {rows}x{steps} one step at a time", flush=True)
+        a, b = solver_for_case(case, prec), solver_for_case(case, prec)
+        for s in (a, b):
+            s.set_tile_march(rows, steps)
+        f, tmp, ck = b.empty_state(), b.empty_state(), [b.empty_state() for _ in range(11)]
+        f.copy_(next(t for t in b._bufs if t.data_ptr() == b.buffers()[0]))
+        b.step_checkpointed(f, tmp, 1, 11, ck)
+        a.step(11)
+        for _ in range(11):
+            b.step(1)
+        got = [next(t for t in s._bufs if t.data_ptr() == s.buffers()[0]) for s in (a, b)]
+        cells = (torch.arange(16, device="cuda")[:, None, None] * a.plane + a.origin
+                 + torch.arange(ny, device="cuda")[None, :, None] * a.pitch + torch.arange(nx, device="cuda"))
+        whole, single, buffers = (t.view(a.storage_dtype)[cells] for t in (*got, f))
+        assert torch.equal(whole, single) and torch.equal(whole, buffers), (nx, ny)
+        a.close()
+        b.close()
