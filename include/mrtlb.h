@@ -134,6 +134,12 @@ int mrt_set_fields(mrt_ctx* ctx, const double* rho, const double* ux, const doub
  * the overlap recomputed; small grids) and one or two steps per pass.  Steps
  * left over take a shorter pass.  Health (NaN, rho <= 0, T <= 0) is
  * recorded on the device and reported by the next synchronising call.
+ * How a number of steps is split over calls changes no bit on the grids of the
+ * marches, with one step per pass (mrt_set_steps_per_pass) and in pure FP32.
+ * With the level pipeline or two steps per pass, whose left-over steps run
+ * another kernel, it changes a few roundings in FP64 and at most the rounding
+ * to storage in FP32 storage with FP64 collision (none seen): a program that
+ * needs the same bits however it steps names one step per pass.
  * Errors: MRT_ESTATE, MRT_EINVAL (n < 0). */
 int mrt_step(mrt_ctx* ctx, int n);
 
@@ -227,11 +233,13 @@ int mrt_get_steps_per_pass(const mrt_ctx* ctx, int* steps, int* rows);
  * other through LDS, so that the state crosses the memory interface once per
  * four steps.  With it on, mrt_step(n) runs n / 4 such passes and the
  * remaining steps by the form of mrt_set_steps_per_pass.  Results equal single
- * steps to rounding order (bit-identical in the FP32 storage forms, as
- * measured).  rows: band height (0: by grid size), -1 turns it off.
+ * steps to rounding order (the same FMA chains, but the FP64 collision's
+ * fusion may differ per copy of the code: bit-identical in pure FP32 and, as
+ * measured, in FP32 storage with FP64 collision; a few roundings in FP64).
+ * rows: band height (0: by grid size), -1 turns it off.
  * mrt_init_grid turns it on where it is expected to be faster than the tile
- * march and than one or two steps per pass (from about 400 x 300 cells on in
- * FP64, 600^2 in FP32 storage; not on the tube march's grids); mrt_autotune
+ * march and than one or two steps per pass (from about 450^2 cells on in
+ * FP64, 650^2 in FP32 storage; not on the tube march's grids); mrt_autotune
  * times them all, and mrt_set_steps_per_pass, which names another form, turns
  * it off, as does mrt_set_tile.  Turning it on or off also ends the tile
  * march.
@@ -245,8 +253,8 @@ int mrt_get_pipeline(const mrt_ctx* ctx, int* rows);
  * holds `rows` rows of 64 columns, advances them `steps` steps and stores the
  * cells that are exact (the overlap of `steps` cells on every side is
  * recomputed by the neighbouring blocks).  Steps left over take one shorter
- * launch.  Results equal single steps to rounding order (bit-identical in
- * pure FP32), and do not depend on how a number of steps is split over calls.
+ * launch.  Results equal single steps to rounding order (as for the level
+ * pipeline), and do not depend on how a number of steps is split over calls.
  * rows: 8, 12 or, in FP32 storage, 16 (0: by grid size), -1 turns it off;
  * steps: 1 to 6, fewer than half the rows (0: by grid size).  mrt_init_grid
  * turns it on for small grids.  Turning it on or off also ends the level
@@ -326,7 +334,8 @@ int mrt_adjoint_step_noalloc(mrt_ctx* ctx, const void* lam_next, const void* f_n
 /* Forward pass that keeps sqrt(N)-style checkpoints for a later
  * mrt_adjoint_sweep: checkpoints[k] receives f^(k * segment) for
  * k * segment < nsteps (f^0 by a copy, the others written there by their
- * step directly), stepping as mrt_step_buffers.  segment = 1 keeps every
+ * step directly), several steps per launch between them where the context
+ * runs the level pipeline or the tile march (mrt_get_form), else one.  segment = 1 keeps every
  * state (no recomputation in the sweep).  f: on entry f^0, on return f^nsteps.  f_tmp: one more
  * state buffer (overwritten).  checkpoints: ceil(nsteps / segment) buffers.
  * All device buffers in the storage precision and padded layout, owned by the
@@ -340,7 +349,9 @@ int mrt_step_checkpointed(mrt_ctx* ctx, void* f, void* f_tmp, int segment, int n
  * forward steps of Eq. 3 (forward Euler, Lax-Wendroff), lam^n =
  * (dF/df^n)^T lam^{n+1} per step as in mrt_adjoint_step, derived from Eq. 3
  * and the Appendix equilibrium.  Segment by segment, newest first, it
- * recomputes f^start+1 .. f^stop-1 from checkpoint f^start into `work`, then
+ * recomputes f^start+1 .. f^stop-1 from checkpoint f^start into `work` (by the
+ * tile march where the context runs it, else one step at a time: where the
+ * forward pass took the level pipeline, equal to its states to rounding), then
  * runs mrt_adjoint_step for n = stop-1 down to start.  The checkpointing
  * keeps ceil(N / segment) + segment states for one extra forward step per
  * step (segment ~ sqrt(N) minimises the memory).

@@ -1682,8 +1682,10 @@ int mrt_adjoint_sweep(mrt_ctx* c, const void* const* checkpoints, int segment, i
     auto state = [&](int seg, int j) -> const void* {
         return j == 0 ? checkpoints[seg] : work[set_of(seg) * w + j - 1];
     };
-    // f^{start + 1} .. f^{stop - 1} of segment seg, as mrt_step_checkpointed
-    // takes them on a periodic grid (no ghost ring to refill)
+    // f^{start + 1} .. f^{stop - 1} of segment seg (a periodic grid: no ghost
+    // ring to refill), as mrt_step_checkpointed takes them but where that runs
+    // the level pipeline, which keeps no state between: one step at a time
+    // then, the same states to rounding
     auto recompute = [&](int seg, hipStream_t st) -> hipError_t {
         const int start = seg * segment, stop = std::min(nsteps, start + segment);
         if (c->tile) {

@@ -1103,7 +1103,7 @@ __device__ __forceinline__ void adjoint_block(ConstInst* __restrict__ P, int ite
     // waves' sums in a fixed order into the item's partial row
     // Halving: each stage a lane keeps half of its values, those its bit of the
     // lane number names, and gives the other half to its partner, so the twelve
-    // sums over 64 lanes take 14 exchanges instead of 72 (the same additions in
+    // sums over 64 lanes take 17 exchanges instead of 72 (the same additions in
     // the same tree: bitwise the same sums).  Lane l ends with sum l / 4.
     double v[16];
 #pragma unroll

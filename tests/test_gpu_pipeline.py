@@ -281,3 +281,27 @@ def test_four_waves_per_level_match_single_steps(shape, rows, bc, prec):
     assert d <= (0.0 if prec == "fp32" else 1e-6), d
     one.close()
     pipe.close()
+
+
+@pytest.mark.parametrize("prec,n,bc", [("fp64", 520, BC_SETS[2]), ("fp32_eq64", 720, BC_SETS[1]),
+                                       ("fp32", 720, BC_SETS[4]), ("fp64", 1040, BC_SETS[0])])
+def test_how_a_number_of_steps_is_split(prec, n, bc):
+    """On grids that run the pipeline by default, nine steps at once (two
+    passes and one left over) against nine calls: to rounding, bit for bit in
+    pure FP32; bit for bit in every precision with one step per pass."""
+    case = smooth_case(n, n, bc, seed=n)
+    print(f"case {case.name} bc={bc} {prec} split step counts", flush=True)
+    for one in (False, True):
+        a, b = solver_for_case(case, prec), solver_for_case(case, prec)
+        assert a.form()[0] == "pipeline"
+        if one:
+            for s in (a, b):
+                s.set_steps_per_pass(1, 0)
+        a.step(9)
+        for _ in range(9):
+            b.step(1)
+        fa, fb = a.populations(), b.populations()
+        d = float(np.max(np.abs(fa - fb)) / np.abs(fb).max())
+        assert d <= (0.0 if one else {"fp64": 1e-13, "fp32_eq64": 2.4e-7, "fp32": 0.0}[prec]), d
+        a.close()
+        b.close()
