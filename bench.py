@@ -46,6 +46,14 @@ MEASURED_TRAFFIC = {
     "fetch_kib": 747054.0, "fetch_copy_kib": 524304.7,
     "write_kib": 1049089.3, "write_copy_kib": 1048576.0,
 }
+# The same for one pipe_kernel launch (four steps) as the headline workload
+# runs by default: four waves per level, bands of 274 rows.
+MEASURED_PIPE_TRAFFIC = {
+    "digest": "0898b534927856f44576f0a98ad16e1dbe923d57a822b5a80b01e8882cc8b7b2",
+    "band_rows": 274,
+    "fetch_kib": 544947.5, "fetch_copy_kib": 524299.5,
+    "write_kib": 1274407.2, "write_copy_kib": 1048576.0,
+}
 STEP_HEADERS = ("mrt_transform.h", "mrt_transform_impl.inc", "mrt_internal.h")
 
 
@@ -58,11 +66,12 @@ def _code_only(text: str) -> str:
     return " ".join(text.split())
 
 
-def kernel_digest() -> str:
+def kernel_digest(pipe=False) -> str:
     """sha256 over what decides the step kernels' memory traffic, comments
     aside: their source (mrt_kernels.hip up to the adjoint section: helpers,
     ghost and step kernels), their launchers, the headers they include, and
-    the population layout (the layout functions of mrt_api.hip)."""
+    the population layout (the layout functions of mrt_api.hip).  pipe: the
+    level pipeline's section, launcher and constants too."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_1004_5442_amd", "csrc")
     with open(os.path.join(csrc, "mrt_kernels.hip")) as fh:
@@ -72,25 +81,32 @@ def kernel_digest() -> str:
     for name in ("hipError_t launch_step(", "hipError_t launch_step2("):
         i0 = text.index(name)
         launchers.append(text[i0:text.index("\n}\n", i0)])
+    headers = STEP_HEADERS
+    if pipe:
+        i0 = text.index("// --------------------------------------------------------- level pipeline")
+        launchers.append(text[i0:text.index("// ------------------------------------------------------------ tile march", i0)])
+        i0 = text.index("hipError_t launch_pipe(")
+        launchers.append(text[i0:text.index("\n}\n", i0)])
+        headers += ("mrt_pipe.h",)
     with open(os.path.join(csrc, "mrt_api.hip")) as fh:
         api = fh.read()
     layout = api[api.index("// Population layout"):api.index("bool bc_ok(")]
     h = hashlib.sha256()
     for part in [head, *launchers, layout]:
         h.update(hashlib.sha256(_code_only(part).encode()).digest())
-    for name in STEP_HEADERS:
+    for name in headers:
         with open(os.path.join(csrc, name)) as fh:
             h.update(hashlib.sha256(_code_only(fh.read()).encode()).digest())
     return h.hexdigest()
 
 
 def measured_traffic(precision, per_pass, band_rows):
-    """HBM bytes per two-step-kernel launch (counter readings scaled by the
-    copy calibration), or None when they do not describe the kernel that
-    runs."""
-    m = MEASURED_TRAFFIC
-    if (precision != "fp32_eq64" or per_pass != 2 or m["digest"] != kernel_digest()
-            or band_rows != m["band_rows"]):
+    """HBM bytes per launch of the two-step kernel (per_pass 2) or the level
+    pipeline (4): counter readings scaled by the copy calibration, or None when
+    they do not describe the kernel that runs."""
+    m = {2: MEASURED_TRAFFIC, 4: MEASURED_PIPE_TRAFFIC}.get(per_pass)
+    if (m is None or precision != "fp32_eq64" or band_rows != m["band_rows"]
+            or m["digest"] != kernel_digest(per_pass == 4)):
         return None
     gib_kib = 1024.0 * 1024.0
     fetch = m["fetch_kib"] * gib_kib / m["fetch_copy_kib"]
@@ -154,6 +170,20 @@ def _configured_solver(case, precision, autotune, tile_rows, scheme, per_pass):
     return s
 
 
+def _take_form(heat, s):
+    """Configure the solver (or batch) `heat` to run in the form that `s` runs in."""
+    form, steps, rows, _ = s.form()
+    heat.set_tile(*s.tile())
+    if form == "pipeline":
+        heat.set_pipeline(rows)
+    elif form == "tile":
+        heat.set_tile_march(rows, steps)
+    elif form == "tube":
+        heat.set_steps_per_pass(4)
+    else:
+        heat.set_steps_per_pass(steps, rows if steps == 2 else 0)
+
+
 def time_solver(case, precision, steps, warmup, autotune=True, tile_rows=0, scheme=None,
                 per_pass=0):
     """per_pass 1 or 2 with tile_rows: that kernel and band height; else the
@@ -162,11 +192,8 @@ def time_solver(case, precision, steps, warmup, autotune=True, tile_rows=0, sche
     import torch
     s = _configured_solver(case, precision, autotune, tile_rows, scheme, per_pass)
     heat = _configured_solver(case, precision, False, tile_rows, scheme, per_pass)
-    if autotune and not tile_rows and not per_pass:
-        heat.set_tile(*s.tile())
-        k, r = s.steps_per_pass()
-        if not scheme and s.pipeline() < 0:
-            heat.set_steps_per_pass(k, r if k == 2 else 0)
+    if autotune and not tile_rows and not per_pass and not scheme:
+        _take_form(heat, s)
     pre = _preheat(heat.step, max_steps=case.nsteps)
     heat.close()
     del heat
@@ -175,20 +202,17 @@ def time_solver(case, precision, steps, warmup, autotune=True, tile_rows=0, sche
     s.sync()
     sec = _events_time(torch.cuda.current_stream(), s.step, steps)
     s.sync()      # raises if the run went unhealthy
-    tile = s.tile()
-    pp = s.steps_per_pass()
-    if s.pipeline() > 0:
-        pp = (4, s.pipeline())       # the level pipeline (what remains of a step count: pp)
+    form, pass_steps, band_rows, _ = s.form()
     s.close()
     mlups = case.cells * steps / sec / 1e6
-    return {"mlups": mlups, "sec": sec, "ms_per_step": 1e3 * sec / steps, "tile": tile,
-            "per_pass": pp[0], "band_rows": pp[1], "preheat_steps": pre}
+    return {"mlups": mlups, "sec": sec, "ms_per_step": 1e3 * sec / steps, "form": form,
+            "per_pass": pass_steps, "band_rows": band_rows, "preheat_steps": pre}
 
 
 def time_batch(steps, warmup, precision="fp32_eq64"):
     """The batched form: 512 seeded shock tubes (nx 200..4000, ny 4), FP32
     populations with FP64 collision (or the given precision), graph-captured
-    passes in the launch the batch autotuner picks (the tube march, four
+    passes in the launch the batch autotuner picks (the tube march, eight
     steps per pass, on this batch); the step counts are rounded up to whole
     passes."""
     import torch
@@ -199,9 +223,8 @@ def time_batch(steps, warmup, precision="fp32_eq64"):
     b = Batch(cases, precision)
     b.autotune(4)
     heat = Batch(cases, precision)
-    heat.set_tile(*b.tile())
-    k, r = b.steps_per_pass()
-    heat.set_steps_per_pass(k, r if k == 2 else 0)
+    _take_form(heat, b)
+    form, k, rows, _ = b.form()
     pre = _preheat(heat.step, max_steps=cases[0].nsteps)
     heat.close()
     del heat
@@ -212,18 +235,29 @@ def time_batch(steps, warmup, precision="fp32_eq64"):
     sec = _events_time(torch.cuda.current_stream(), b.step, steps)
     b.moments(0)              # raises if any instance went unhealthy
     cells = b.cells
-    tile = b.tile()
-    pp = b.steps_per_pass()
     b.close()
     return {"mlups": round(cells * steps / sec / 1e6, 1), "cells": cells, "instances": len(cases),
-            "ms_per_step": round(1e3 * sec / steps, 4), "steps": steps, "tile_rows": tile[0],
-            "kernel": {1: "step_kernel", 2: "step2_kernel", 4: "tube_kernel"}[pp[0]],
-            "steps_per_pass": pp[0], "band_rows": pp[1], "preheat_steps": pre,
-            "roofline_frac": round(cells * BYTES_PER_SITE[precision] * steps / sec / 1e9 / HBM_PEAK_GBS, 4)}
+            "ms_per_step": round(1e3 * sec / steps, 4), "steps": steps, "kernel": _kernel(form, k),
+            "steps_per_pass": k, "band_rows": rows, "preheat_steps": pre,
+            "per_step_bytes_frac": round(cells * BYTES_PER_SITE[precision] * steps / sec / 1e9 / HBM_PEAK_GBS, 4)}
+
+
+def _default_step(sv, rho0, T0, steps):
+    """Seconds per step of the solver's default form from these fields."""
+    import torch
+    zero = torch.zeros_like(rho0)
+    sv.set_fields(rho0, zero, zero, T0)
+    steps = -(-steps // 60) * 60             # whole passes of every form
+    sv.step(steps)
+    sv.prepare(steps)
+    sec = _events_time(torch.cuda.current_stream(), sv.step, steps) / steps
+    sv.sync()
+    return sec
 
 
 def time_adjoint_large(n, steps):
-    """Adjoint step vs forward step on an n^2 periodic grid of the adjoint
+    """Adjoint step vs forward step (the one-step kernel between buffers, and
+    a step of the solver's default form) on an n^2 periodic grid of the adjoint
     workload's kind (FP32 storage, FP64 collision), large enough to leave the
     caches: the adjoint moves 192 B per site (lam read, f read, lam write)."""
     import torch
@@ -257,15 +291,18 @@ def time_adjoint_large(n, steps):
     st = torch.cuda.current_stream()
     t_f = _events_time(st, fwd, steps) / steps
     t_a = _events_time(st, adj, steps) / steps
+    t_d = _default_step(sv, rho0, T0, steps)
     sv.close()
     return {"grid": f"{n}x{n}", "adjoint_step_ms": round(1e3 * t_a, 4), "forward_step_ms": round(1e3 * t_f, 4),
-            "adjoint_over_forward": round(t_a / t_f, 3), "adjoint_mlups": round(n * n / t_a / 1e6, 1),
+            "default_forward_step_ms": round(1e3 * t_d, 4),
+            "adjoint_over_forward": round(t_a / t_f, 3), "adjoint_over_default_forward": round(t_a / t_d, 3),
+            "adjoint_mlups": round(n * n / t_a / 1e6, 1),
             "adjoint_roofline_frac": round(n * n * 192 / t_a / 1e9 / HBM_PEAK_GBS, 4)}
 
 
 def time_adjoint(steps):
-    """Adjoint step vs forward step on the 256^2 periodic adjoint workload
-    (FP32 storage, FP64 collision), and one full gradient (500-step forward,
+    """Adjoint step vs forward step (as time_adjoint_large) on the 256^2
+    periodic adjoint workload (FP32 storage, FP64 collision), and one full gradient (500-step forward,
     sqrt(N) checkpoints, backward) vs the plain 500-step forward (each the
     median of five runs)."""
     import torch
@@ -327,9 +364,11 @@ def time_adjoint(steps):
     t_fwd_full = median_s(fwd_full)
     grad()          # the first backward also starts autograd's device threads
     t_grad = median_s(grad)
+    t_d = _default_step(sv, rho0, T0, steps)
     sv.close()
     return {"grid": f"{n}x{n}", "adjoint_step_ms": round(1e3 * t_a, 4), "forward_step_ms": round(1e3 * t_f, 4),
-            "adjoint_over_forward": round(t_a / t_f, 3),
+            "default_forward_step_ms": round(1e3 * t_d, 4),
+            "adjoint_over_forward": round(t_a / t_f, 3), "adjoint_over_default_forward": round(t_a / t_d, 3),
             "adjoint_mlups": round(n * n / t_a / 1e6, 1),
             "adjoint_roofline_frac": round(n * n * 192 / t_a / 1e9 / HBM_PEAK_GBS, 4),
             "gradient_500_steps_s": round(t_grad, 4), "forward_500_steps_s": round(t_fwd_full, 4),
@@ -337,27 +376,43 @@ def time_adjoint(steps):
             "note": "256^2 FP32 fits the Infinity Cache: effective, not HBM, bandwidth"}
 
 
+def _kernel(form, per_pass):
+    return {"pipeline": "pipe_kernel", "tile": "tile_kernel", "tube": "tube_kernel"}.get(
+        form, "step2_kernel" if per_pass == 2 else "step_kernel")
+
+
 def roofline(case, precision, r, traffic=None):
-    """Algorithmic bytes of one step-kernel launch (bytes per site update x
-    the site updates of one launch: cells x steps per pass) over the
-    event-timed launch (which also holds the ~5 us reflecting-wall ghost
-    launch: achieved is a slight underestimate of the kernel's own rate)."""
-    per_pass = r.get("per_pass", 1)
-    per_launch_bytes = BYTES_PER_SITE[precision] * case.cells * per_pass
-    achieved = per_launch_bytes / (r["sec"] / r["steps"] * per_pass) / 1e9
-    out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    """Algorithmic bytes of one launch over the event-timed launch (which also
+    holds the ~5 us reflecting-wall ghost launch where there is one: achieved is
+    a slight underestimate of the kernel's own rate).  One and two steps per
+    pass: bytes per site update x the site updates of a launch (cells x steps).
+    The forms of more steps move the state once per launch, which is what
+    their launch is charged with; per_step_bytes_frac keeps the per-step
+    bytes over the peak for every form (above 1 where several steps share one
+    crossing)."""
+    per_pass, form = r.get("per_pass", 1), r.get("form", "steps")
+    launch_s = r["sec"] / r["steps"] * per_pass
+    per_step_gbs = BYTES_PER_SITE[precision] * case.cells * per_pass / launch_s / 1e9
+    per_launch_bytes = BYTES_PER_SITE[precision] * case.cells * (per_pass if form == "steps" else 1)
+    achieved = per_launch_bytes / launch_s / 1e9
+    bound = "hbm"
+    if form != "steps":
+        bound = "latency" if precision == "fp64" or form == "tile" else "valu"
+    out = {"bound": bound, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
            "traffic_unit": "bytes per launch", "algorithmic_bytes": per_launch_bytes,
-           "kernel": {4: "pipe_kernel", 2: "step2_kernel"}.get(per_pass, "step_kernel"),
+           "per_step_bytes_GBs": round(per_step_gbs, 1),
+           "per_step_bytes_frac": round(per_step_gbs / HBM_PEAK_GBS, 4),
+           "kernel": _kernel(form, per_pass),
            "bytes_per_site": BYTES_PER_SITE[precision], "site_updates_per_launch": case.cells * per_pass}
     if traffic is not None:
         # what the launch really moves, per second (counter readings)
-        out["traffic_GBs"] = round(traffic / (r["sec"] / r["steps"] * per_pass) / 1e9, 1)
-    if per_pass == 4:
+        out["traffic_GBs"] = round(traffic / launch_s / 1e9, 1)
+    if form == "pipeline":
         out["note"] = ("four time steps per launch: the state crosses the memory interface once per "
-                       "launch, about 0.28 x the per-step algorithmic bytes; bound by vector "
-                       "instructions (FP32 storage) or by that traffic (FP64)")
-    if per_pass == 2:
+                       "launch; FP32 storage is bound by vector instruction issue, FP64 (two waves per "
+                       "SIMD, a barrier per row) by neither that nor memory alone")
+    if form == "steps" and per_pass == 2:
         out["note"] = ("two time steps per launch: each launch reads f^n once and writes f^{n+2}, so "
                        "its HBM traffic (traffic_GBs) is about 0.61 x the per-step algorithmic bytes; "
                        "that traffic moves at ~4.6-4.7 TB/s, near the 4.7-5.3 TB/s that plain "
@@ -466,40 +521,41 @@ def extra_legs(head, prec, steps):
         r1 = time_solver(head, prec, k, 3, tile_rows=HEADLINE_TILE_ROWS, per_pass=1)
         r1["steps"] = k
         return {"mlups": round(r1["mlups"], 1), "band_rows": HEADLINE_TILE_ROWS,
-                "roofline_frac": roofline(head, prec, r1)["frac"]}
+                "per_step_bytes_frac": roofline(head, prec, r1)["per_step_bytes_frac"]}
 
     def two_step():
         r2 = time_solver(head, prec, k, 3, tile_rows=HEADLINE_BAND_ROWS, per_pass=2)
         r2["steps"] = k
         return {"mlups": round(r2["mlups"], 1), "band_rows": HEADLINE_BAND_ROWS,
-                "roofline_frac": roofline(head, prec, r2)["frac"]}
+                "per_step_bytes_frac": roofline(head, prec, r2)["per_step_bytes_frac"]}
 
     def fp64():
         # the library's default at this size
         r64 = time_solver(head, "fp64", k, 3, per_pass=4)
         r64["steps"] = k
         return {"mlups": round(r64["mlups"], 1), "steps_per_pass": r64["per_pass"],
-                "band_rows": r64["band_rows"], "roofline_frac": roofline(head, "fp64", r64)["frac"]}
+                "form": r64["form"], "band_rows": r64["band_rows"],
+                "per_step_bytes_frac": roofline(head, "fp64", r64)["per_step_bytes_frac"]}
 
     def fp64_one_step():
         r64 = time_solver(head, "fp64", k, 3, tile_rows=HEADLINE_TILE_ROWS)
         r64["steps"] = k
         return {"mlups": round(r64["mlups"], 1), "band_rows": HEADLINE_TILE_ROWS,
-                "roofline_frac": roofline(head, "fp64", r64)["frac"]}
+                "per_step_bytes_frac": roofline(head, "fp64", r64)["per_step_bytes_frac"]}
 
     def fp32():
         r32 = time_solver(head, "fp32", k, 3, per_pass=4)
         r32["steps"] = k
-        return {"mlups": round(r32["mlups"], 1), "steps_per_pass": r32["per_pass"],
-                "roofline_frac": roofline(head, "fp32", r32)["frac"]}
+        return {"mlups": round(r32["mlups"], 1), "steps_per_pass": r32["per_pass"], "form": r32["form"],
+                "per_step_bytes_frac": roofline(head, "fp32", r32)["per_step_bytes_frac"]}
 
     def riemann(pr):
         def run():
             rp = W.riemann2d(n=1024, seed=0)
             rr = time_solver(rp, pr, 2 * k, 5)
             rr["steps"] = 2 * k
-            return {"mlups": round(rr["mlups"], 1), "steps_per_pass": rr["per_pass"],
-                    "effective_GBs": roofline(rp, pr, rr)["achieved"],
+            return {"mlups": round(rr["mlups"], 1), "steps_per_pass": rr["per_pass"], "form": rr["form"],
+                    "effective_GBs": roofline(rp, pr, rr)["per_step_bytes_GBs"],
                     "note": "fits the 256 MB Infinity Cache: effective, not HBM, bandwidth"}
         return run
 
@@ -511,8 +567,8 @@ def extra_legs(head, prec, steps):
         c = W.shock_bubble(n=4096, ny=512)
         rr = time_solver(c, prec, 2 * k, 5)
         rr["steps"] = 2 * k
-        return {"mlups": round(rr["mlups"], 1), "steps_per_pass": rr["per_pass"],
-                "band_rows": rr["band_rows"], "effective_GBs": roofline(c, prec, rr)["achieved"],
+        return {"mlups": round(rr["mlups"], 1), "steps_per_pass": rr["per_pass"], "form": rr["form"],
+                "band_rows": rr["band_rows"], "effective_GBs": roofline(c, prec, rr)["per_step_bytes_GBs"],
                 "note": "4096 x 512: one GPU's share at eight; fits the 256 MB Infinity Cache"}
 
     def variants():
@@ -521,7 +577,7 @@ def extra_legs(head, prec, steps):
                                ("split_lw_cross", {"split": True, "lw_cross": True}, 256)):
             rv = time_solver(head, prec, k, 3, autotune=False, scheme=sch)
             out[name] = {"mlups": round(rv["mlups"], 1), "bytes_per_site": bps,
-                         "roofline_frac": round(bps * rv["mlups"] * 1e6 / 1e9 / HBM_PEAK_GBS, 4)}
+                         "per_step_bytes_frac": round(bps * rv["mlups"] * 1e6 / 1e9 / HBM_PEAK_GBS, 4)}
         return out
 
     def rm(pr):
@@ -529,8 +585,9 @@ def extra_legs(head, prec, steps):
             rr = time_solver(W.rm_instability(), pr, 4 * k, 64)
             rr["steps"] = 4 * k
             return {"mlups": round(rr["mlups"], 1), "ms_per_step": round(rr["ms_per_step"], 5),
-                    "tile_rows": rr["tile"][0], "steps_per_pass": rr["per_pass"],
-                    "note": "36,000 cells: launch-latency bound (captured graphs of 64 steps)"}
+                    "form": rr["form"], "steps_per_pass": rr["per_pass"], "band_rows": rr["band_rows"],
+                    "note": "36,000 cells: bound by launches and a level's chain of instructions "
+                            "(captured graphs of 64 passes, the autotuner's form)"}
         return run
 
     def paper_riemann2d():
@@ -539,8 +596,8 @@ def extra_legs(head, prec, steps):
         c = W.paper_riemann2d()
         rr = time_solver(c, "fp64", 4 * k, 5)
         rr["steps"] = 4 * k
-        return {"mlups": round(rr["mlups"], 1), "steps_per_pass": rr["per_pass"],
-                "effective_GBs": roofline(c, "fp64", rr)["achieved"],
+        return {"mlups": round(rr["mlups"], 1), "steps_per_pass": rr["per_pass"], "form": rr["form"],
+                "effective_GBs": roofline(c, "fp64", rr)["per_step_bytes_GBs"],
                 "note": "fits the 256 MB Infinity Cache: effective, not HBM, bandwidth"}
 
     def strong_shock():
@@ -549,10 +606,10 @@ def extra_legs(head, prec, steps):
         c = W.strong_shock_tube(1.4, False)
         rr = time_solver(c, "fp64", 16 * k, 64)
         return {"mlups": round(rr["mlups"], 1), "ms_per_step": round(rr["ms_per_step"], 5),
-                "steps_per_pass": rr["per_pass"],
+                "steps_per_pass": rr["per_pass"], "form": rr["form"],
                 "steps_for_t_0.13_s": round(c.nsteps * rr["ms_per_step"] / 1e3, 3),
-                "note": "1,100 cells: launch-latency bound (captured graphs of 64 passes; the "
-                        "autotuner's steps per pass, 4 = the tube march)"}
+                "note": "1,100 cells: bound by a level's chain of instructions (captured graphs of "
+                        "64 passes; the autotuner's form)"}
 
     return {
         "device_copy_1gib": device_copy,
@@ -641,7 +698,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"shock_bubble {n}x{n} (Mach-5 shock on a density-3 bubble, "
                                f"gamma 1.4, Pr 0.71, reflect/inflow/outflow)",
-                   "cells": head.cells, "precision": prec, "steps_per_pass": r["per_pass"],
+                   "cells": head.cells, "precision": prec, "form": r["form"], "steps_per_pass": r["per_pass"],
                    "band_rows": r["band_rows"]},
         "roofline": roofline(head, prec, r, measured_traffic(prec, r["per_pass"], r["band_rows"])),
     }

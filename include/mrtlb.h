@@ -449,6 +449,9 @@ int mrt_batch_get_tile(const mrt_batch* b, int* rows_per_item, int* grid_blocks)
  * the tube march does not cover). */
 int mrt_batch_set_steps_per_pass(mrt_batch* b, int steps, int rows);
 int mrt_batch_get_steps_per_pass(const mrt_batch* b, int* steps, int* rows);
+/* As mrt_get_form, for mrt_batch_step (MRT_FORM_STEPS or MRT_FORM_TUBE, whose
+ * passes take more steps than the 4 that name it). */
+int mrt_batch_get_form(const mrt_batch* b, int* form, int* steps, int* rows, int* waves);
 int mrt_batch_autotune(mrt_batch* b, int steps_per_trial);
 long long mrt_batch_cells(const mrt_batch* b);
 void mrt_batch_destroy(mrt_batch* b);

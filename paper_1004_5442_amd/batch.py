@@ -83,6 +83,13 @@ class Batch:
         self._check(L.raw().mrt_batch_get_steps_per_pass(self._h, byref(k), byref(r)))
         return k.value, r.value
 
+    def form(self):
+        """(form, steps of a pass, rows, waves) of whole passes
+        (mrt_batch_get_form; form: one of lib.FORM)."""
+        out = [c_int() for _ in range(4)]
+        self._check(L.raw().mrt_batch_get_form(self._h, *[byref(v) for v in out]))
+        return (L.FORM[out[0].value],) + tuple(v.value for v in out[1:])
+
     def autotune(self, steps: int = 8):
         self._check(L.raw().mrt_batch_autotune(self._h, int(steps)))
         return self.tile()

@@ -2186,6 +2186,16 @@ int mrt_batch_get_steps_per_pass(const mrt_batch* b, int* steps, int* rows) {
     return MRT_OK;
 }
 
+int mrt_batch_get_form(const mrt_batch* b, int* form, int* steps, int* rows, int* waves) {
+    if (!b) return MRT_EINVAL;
+    const bool tube = b->per_pass == kTubeSteps;
+    if (form) *form = tube ? MRT_FORM_TUBE : MRT_FORM_STEPS;
+    if (steps) *steps = tube ? b->tube.steps : b->per_pass;
+    if (rows) *rows = tube ? b->tube_ny : (b->per_pass == 2 ? b->rows2 : b->rows);
+    if (waves) *waves = tube ? b->tube.waves : 0;
+    return MRT_OK;
+}
+
 int mrt_batch_get_tile(const mrt_batch* b, int* rows, int* grid) {
     if (!b) return MRT_EINVAL;
     if (rows) *rows = b->rows;

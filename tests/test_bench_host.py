@@ -44,3 +44,30 @@ def test_traffic_reading_is_tied_to_the_kernel_sources():
         assert bench.measured_traffic("fp32_eq64", 2, bench.HEADLINE_BAND_ROWS) is None
     finally:
         bench.MEASURED_TRAFFIC.update(saved)
+
+
+def test_pipeline_traffic_is_tied_to_its_sources():
+    """As the two-step kernel's: the default form of the headline grid reports
+    the bytes counted for it, and no other launch does."""
+    rows = bench.MEASURED_PIPE_TRAFFIC["band_rows"]
+    assert bench.measured_traffic("fp32_eq64", 4, rows) is not None
+    assert bench.measured_traffic("fp32_eq64", 4, rows - 1) is None
+    assert bench.measured_traffic("fp64", 4, rows) is None
+    assert bench.kernel_digest(True) != bench.kernel_digest()
+    from paper_1004_5442_amd import lib
+    assert lib.host_default_form(4096, 4096, "fp32_eq64", ("eq", "outflow", "reflect", "reflect")) == (
+        "pipeline", 4, rows, 4)
+
+
+def test_roofline_charges_a_launch_of_several_steps_with_one_crossing():
+    class Case:
+        cells = 4096 * 4096
+    run = {"sec": 20 * 0.2e-3, "steps": 20, "per_pass": 4, "form": "pipeline"}
+    out = bench.roofline(Case, "fp32_eq64", run, traffic=2_400_000_000)
+    assert out["kernel"] == "pipe_kernel" and out["bound"] == "valu"
+    assert out["algorithmic_bytes"] == 128 * Case.cells and 0 < out["frac"] < 1
+    assert abs(out["per_step_bytes_frac"] - 4 * out["frac"]) < 1e-3
+    assert out["traffic_GBs"] == 3000.0
+    two = bench.roofline(Case, "fp32_eq64", {"sec": 1.0, "steps": 2000, "per_pass": 2, "form": "steps"})
+    assert two["bound"] == "hbm" and two["algorithmic_bytes"] == 256 * Case.cells
+    assert two["frac"] == two["per_step_bytes_frac"]

@@ -317,3 +317,17 @@ def test_large_batches_take_wide_blocks(ny, precision):
         assert d <= {"fp64": 1e-13, "fp32_eq64": 2.4e-7, "fp32": 0.0}[precision], (i, d)
     one.close()
     tube.close()
+
+
+def test_a_batch_tells_its_form():
+    """mrt_batch_get_form: the steps that a pass of the tube march really
+    takes, and the form named in its place."""
+    b = Batch(W.tube_batch(6, seed=2, nx_range=(200, 300)), "fp32_eq64")
+    form, steps, rows, waves = b.form()
+    assert form == "tube" and steps >= 8 and rows == 4 and waves in (1, 2)
+    assert b.steps_per_pass() == (4, 4)
+    b.set_steps_per_pass(2, 4)
+    assert b.form() == ("steps", 2, 4, 0)
+    b.set_steps_per_pass(1)
+    assert b.form()[:2] == ("steps", 1)
+    b.close()
