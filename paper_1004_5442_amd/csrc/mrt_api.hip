@@ -407,7 +407,11 @@ PipeShape pipe_shape(int nx, int ny, int prec, int rows) {
 // blocks than CUs) 5.6, the one-step kernel 4.6; 360 x 100 with a wall 8 x 2 4.5,
 // 12 x 4 4.5, 12 x 3 4.8, one step 5.3; FP64 256^2 12 x 3 4.3, 8 x 2 5.6, one step
 // 6.2; 400 x 300 (two rounds) 12 x 3 7.8, as the pipeline; 500^2 12.1 against the
-// pipeline's 10.2.
+// pipeline's 10.2.  Over several rounds of blocks, FP32 storage with FP64
+// collision (one-step kernel, pipeline): 400^2 16 x 2 4.9 (8.5, 8.6), 450^2 12 x
+// 2 7.2 (8.7, 8.7), 500^2 16 x 3 7.5 (9.4, 9.5), 600^2 16 x 2 9.9 (14.4, 10.2),
+// 700^2 16 x 2 13.5 (16.2, 12.3: the model is 10 % off there); all-FP32 within
+// 5 % of these.
 struct TileShape {
     int rows = 8, steps = 1;
     double us = -1;
