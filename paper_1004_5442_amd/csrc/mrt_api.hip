@@ -311,6 +311,23 @@ void add_items(std::vector<Item>& items, int inst, int nx, int ny, int rows, int
     }
 }
 
+// Puts a table of work items on the device in the place of *d (n items).  Where
+// that fails, the old table stays: the form that uses it goes on with the shape
+// it has, instead of launching on a table that is gone.
+hipError_t replace_items(Item** d, int* n, const std::vector<Item>& items) {
+    Item* fresh = nullptr;
+    hipError_t e = hipMalloc(&fresh, items.size() * sizeof(Item));
+    if (e == hipSuccess) e = hipMemcpy(fresh, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        if (fresh) (void)hipFree(fresh);
+        return e;
+    }
+    if (*d) (void)hipFree(*d);
+    *d = fresh;
+    *n = int(items.size());
+    return hipSuccess;
+}
+
 // Short bands (at most 6 rows) and many blocks: the step streams best with
 // ~8-16k blocks of short marches (measured on the 4096^2 grid); small grids
 // go down to one-row bands so that they still spread over the chip.
@@ -645,11 +662,7 @@ int build_items(mrt_ctx* c, int rows) {
     std::string& ctx_err = c->err;
     std::vector<Item> items;
     add_items(items, 0, c->nx, c->ny, rows);
-    if (c->d_items) HIPTRY(hipFree(c->d_items));
-    c->d_items = nullptr;
-    HIPTRY(hipMalloc(&c->d_items, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(c->d_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    c->nitems = int(items.size());
+    HIPTRY(replace_items(&c->d_items, &c->nitems, items));
     c->rows = rows;
     c->graphs.clear();
     return MRT_OK;
@@ -667,11 +680,7 @@ int build_items2(mrt_ctx* c, int rows) {
     std::string& ctx_err = c->err;
     std::vector<Item> items;
     add_items(items, 0, c->nx, c->ny, rows);
-    if (c->d_items2) HIPTRY(hipFree(c->d_items2));
-    c->d_items2 = nullptr;
-    HIPTRY(hipMalloc(&c->d_items2, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(c->d_items2, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    c->nitems2 = int(items.size());
+    HIPTRY(replace_items(&c->d_items2, &c->nitems2, items));
     c->rows2 = rows;
     c->wrap4 = wraps_four_rows(c->inst, rows);
     c->graphs2.clear();
@@ -693,13 +702,10 @@ void add_tube_items(std::vector<Item>& items, int inst, int nx, int ny, const Tu
 int build_items4(mrt_ctx* c) {
     std::string& ctx_err = c->err;
     std::vector<Item> items;
-    c->tube = tube_shape({c->nx}, c->ny, c->prec);
-    add_tube_items(items, 0, c->nx, c->ny, c->tube);
-    if (c->d_items4) HIPTRY(hipFree(c->d_items4));
-    c->d_items4 = nullptr;
-    HIPTRY(hipMalloc(&c->d_items4, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(c->d_items4, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    c->nitems4 = int(items.size());
+    const TubeShape shape = tube_shape({c->nx}, c->ny, c->prec);
+    add_tube_items(items, 0, c->nx, c->ny, shape);
+    HIPTRY(replace_items(&c->d_items4, &c->nitems4, items));
+    c->tube = shape;
     c->graphs4.clear();
     return MRT_OK;
 }
@@ -708,11 +714,7 @@ int build_items_pipe(mrt_ctx* c, const PipeShape& shape) {
     std::string& ctx_err = c->err;
     std::vector<Item> items;
     add_items(items, 0, c->nx, c->ny, shape.rows, mrt::pipe_width(shape.waves));
-    if (c->d_items_p) HIPTRY(hipFree(c->d_items_p));
-    c->d_items_p = nullptr;
-    HIPTRY(hipMalloc(&c->d_items_p, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(c->d_items_p, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    c->nitems_p = int(items.size());
+    HIPTRY(replace_items(&c->d_items_p, &c->nitems_p, items));
     c->rows_p = shape.rows;
     c->waves_p = shape.waves;
     c->graphs_p.clear();
@@ -736,15 +738,10 @@ int build_items_tile(mrt_ctx* c, const TileShape& shape) {
         std::vector<Item> items;
         for (int y = 0; y < c->ny; y += h)
             for (int x = 0; x < c->nx; x += w) items.push_back(Item{0, x, y, std::min(c->ny, y + h)});
-        if (*d) (void)hipFree(*d);
-        *d = nullptr;
-        const hipError_t e = hipMalloc(d, items.size() * sizeof(Item));
-        if (e != hipSuccess) return e;
-        *n = int(items.size());
-        return hipMemcpy(*d, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice);
+        return replace_items(d, n, items);
     };
-    HIPTRY(table(shape.rows, shape.steps, &c->d_items_t, &c->nitems_t));
     if (!c->d_items_t1) HIPTRY(table(kTileOneRows, 1, &c->d_items_t1, &c->nitems_t1));
+    HIPTRY(table(shape.rows, shape.steps, &c->d_items_t, &c->nitems_t));
     c->tile_form = shape;
     c->graphs_t.clear();
     return MRT_OK;
@@ -1852,11 +1849,7 @@ int batch_items(mrt_batch* b, int rows) {
         b->insts[i].item0 = int(items.size());
         add_items(items, i, b->insts[i].nx, b->insts[i].ny, std::min(rows, b->insts[i].ny));
     }
-    if (b->d_items) HIPTRY(hipFree(b->d_items));
-    b->d_items = nullptr;
-    HIPTRY(hipMalloc(&b->d_items, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(b->d_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    b->nitems = int(items.size());
+    HIPTRY(replace_items(&b->d_items, &b->nitems, items));
     b->rows = rows;
     b->graphs.clear();
     return MRT_OK;
@@ -1869,11 +1862,7 @@ int batch_items2(mrt_batch* b, int rows) {
     std::vector<Item> items;
     for (int i = 0; i < b->count; ++i)
         add_items(items, i, b->insts[i].nx, b->insts[i].ny, std::min(rows, b->insts[i].ny));
-    if (b->d_items2) HIPTRY(hipFree(b->d_items2));
-    b->d_items2 = nullptr;
-    HIPTRY(hipMalloc(&b->d_items2, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(b->d_items2, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    b->nitems2 = int(items.size());
+    HIPTRY(replace_items(&b->d_items2, &b->nitems2, items));
     b->rows2 = rows;
     b->wrap4 = false;
     for (int i = 0; i < b->count; ++i) b->wrap4 = b->wrap4 || wraps_four_rows(b->insts[i], rows);
@@ -1896,14 +1885,11 @@ int batch_items4(mrt_batch* b) {
     std::vector<Item> items;
     std::vector<int> nx;
     for (const Inst& I : b->insts) nx.push_back(I.nx);
-    b->tube = tube_shape(nx, b->insts[0].ny, b->prec);
-    for (int i = 0; i < b->count; ++i) add_tube_items(items, i, b->insts[i].nx, b->insts[i].ny, b->tube);
+    const TubeShape shape = tube_shape(nx, b->insts[0].ny, b->prec);
+    for (int i = 0; i < b->count; ++i) add_tube_items(items, i, b->insts[i].nx, b->insts[i].ny, shape);
+    HIPTRY(replace_items(&b->d_items4, &b->nitems4, items));
+    b->tube = shape;
     b->tube_ny = b->insts[0].ny;
-    if (b->d_items4) HIPTRY(hipFree(b->d_items4));
-    b->d_items4 = nullptr;
-    HIPTRY(hipMalloc(&b->d_items4, items.size() * sizeof(Item)));
-    HIPTRY(hipMemcpy(b->d_items4, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice));
-    b->nitems4 = int(items.size());
     b->graphs4.clear();
     return MRT_OK;
 }
