@@ -953,6 +953,7 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
     const bool xwall = c->bc[0] == MRT_BC_REFLECT || c->bc[1] == MRT_BC_REFLECT;
     // a caller's graph may be replayed on a state of another form
     const bool recording = launch && reflect && is_recording(c->stream);
+    bool left_over = false;
     if (c->pipe && c->scheme == 0 && n >= kPipeSteps) {
         // the level pipeline, four steps a pass; the remaining steps by the
         // forms below.  It forms the y-wall ghosts itself and reads those of
@@ -979,6 +980,7 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
         c->recorded |= recording;
         n -= passes * kPipeSteps;
         if (n == 0) return MRT_OK;
+        left_over = true;
     }
     if (c->tile && c->scheme == 0) {
         // the tile march: passes of tile_form.steps steps, then one of the
@@ -1091,7 +1093,10 @@ static int step_impl(mrt_ctx* c, int n, bool launch) {
         return mrt::k_step(c->prec, c->d_inst, c->d_items, c->nitems, c->f[cur], c->f[1 - cur],
                            c->d_health, c->grid, c->nt, c->walls, st);
     };
-    if (n == 1 || c->eager) {
+    // (one to three steps that the pipeline left over: a graph of them would be
+    // captured in the middle of the call, from a start buffer that
+    // mrt_prepare_steps cannot foresee)
+    if (n == 1 || c->eager || left_over) {
         if (!launch) return MRT_OK;
         for (int k = 0; k < n; ++k) {
             HIPTRY(enqueue(c->cur, c->stream));

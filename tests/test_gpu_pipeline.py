@@ -305,3 +305,26 @@ def test_how_a_number_of_steps_is_split(prec, n, bc):
         assert d <= (0.0 if one else {"fp64": 1e-13, "fp32_eq64": 2.4e-7, "fp32": 0.0}[prec]), d
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_eq64"])
+@pytest.mark.parametrize("bc", BC_SETS[:4])
+def test_steps_left_over_after_prepared_passes(bc, prec):
+    """One to three steps left over by the pipeline, launched directly, after
+    prepared graphs and from either start buffer."""
+    case = smooth_case(300, 40, bc, seed=31)
+    print(f"case {case.name} bc={bc} {prec} left-over steps", flush=True)
+    s = solver_for_case(case, prec)
+    s.set_pipeline(0)
+    total = 0
+    for n in (6, 7, 9, 11, 14, 3):
+        s.prepare(n)
+        s.step(n)
+        total += n
+    want, p = oracle_run(case, total)
+    if prec == "fp64":
+        assert np.max(np.abs(s.populations() - want)) <= 1e-12 * np.abs(want).max()
+    else:
+        err = field_errors(s.moments(), mrt.macroscopic(want, p.b))
+        assert max(err.values()) < 1e-5, err
+    s.close()
